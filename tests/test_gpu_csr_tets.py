@@ -98,3 +98,17 @@ def test_bad_vertex_ids(msc):
         with pytest.raises(Exception):
             build(msc, 5, np.array([[0, 1, 2, 3], bad], np.int32))
     check(msc, 5, np.array([[0, 1, 2, 3], [1, 2, 3, 4]], np.int32), "after")
+
+
+@pytest.mark.parametrize("n,ntets", [(300, 511), (300, 512), (300, 513),
+                                     (127, 60), (128, 60), (129, 60),
+                                     (100000, 1500), (130, 6000)])
+def test_block_edges(msc, n, ntets):
+    """Around the 512 tetrahedra and the 128 rows of a block, a block whose
+    vertices are all distinct, and rows too long for a block's LDS (130
+    vertices, each with nearly all others as neighbours, many times over)."""
+    rng = np.random.default_rng(7 * n + ntets)
+    tets = rng.integers(0, n, size=(ntets, 4)).astype(np.int32)
+    if n >= 4 * ntets:
+        tets = rng.permutation(n)[:4 * ntets].reshape(-1, 4).astype(np.int32)
+    check(msc, n, tets, f"edges n={n} T={ntets}")
