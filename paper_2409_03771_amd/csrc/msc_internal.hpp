@@ -52,7 +52,8 @@ enum Counter : int {
   kCtrExits = 5,     // exits over all tiles (from the scan)
   kCtrBadIndex = 6,  // out-of-range CSR column seen
   kCtrOverflow = 7,  // pair table full (bit 0), broken exit chain (bit 1),
-                     // in-tile jumping did not settle (bit 2)
+                     // in-tile jumping did not settle (bit 2), first pair
+                     // table full (bit 4: the pair pass runs again)
   kCtrRounds = 9,    // longest exit chain walked
   kCtrSteps = 10,    // exit-graph links followed in total
   kCtrRootsMax = 11, // vertices that are their own ascent label

@@ -66,6 +66,10 @@ struct Cfg {
 
 constexpr unsigned long long kEmptyKey = ~0ull;
 
+// Bits of the overflow counter that the pair passes set: the first table had
+// no room (the second pass then runs on the full capacity), or the full one.
+constexpr unsigned long long kOverflowFirst = 16ull, kOverflowFull = 1ull;
+
 // Per-field counters (kFieldCtrs per field).
 enum FieldCtr : int { kFMaxima = 0, kFMinima = 1, kFCells = 2, kFNaN = 3,
                       kFExits = 4, kFieldCtrs = 5 };
@@ -274,17 +278,6 @@ struct BlockTile {
   FieldDev fd;
 };
 
-__device__ __forceinline__ BlockTile block_tile_at(const FieldDev *fds,
-                                                   const uint32_t *tfield,
-                                                   uint32_t blk, uint32_t nb) {
-  BlockTile b;
-  b.gt = tile_of_block(blk, nb);
-  b.fi = tfield[b.gt];
-  b.fd = fds[b.fi];
-  b.tile = b.gt - b.fd.tile0;
-  return b;
-}
-
 __device__ __forceinline__ BlockTile block_tile(const FieldDev *fds,
                                                 const uint32_t *tfield) {
   BlockTile b;
@@ -351,13 +344,17 @@ __device__ __forceinline__ void fold_stat(bool in, uint32_t v, uint32_t fi,
   }
 }
 
+// Marks, in a tile's cell counter, a tile that the pair pass left to the slab
+// pass (the counter itself stays below it).
+constexpr uint32_t kTilePending = 0x80000000u;
+
 __global__ void __launch_bounds__(kBlock)
 k_tile_stat_reduce(const uint32_t *__restrict__ tstat, int k, uint32_t nt,
                    const uint32_t *__restrict__ tfield,
                    unsigned long long *fctr, int which) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   const bool in = i < nt;
-  const uint32_t v = in ? tstat[4 * (size_t)i + k] : 0u;
+  const uint32_t v = in ? tstat[4 * (size_t)i + k] & ~kTilePending : 0u;
   const uint32_t fi = in ? tfield[i] : 0u;
   fold_stat(in, v, fi, fctr, which);
 }
@@ -1074,6 +1071,11 @@ __device__ __forceinline__ uint32_t load_dev(const uint32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ unsigned long long load_dev64(
+    const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ void __launch_bounds__(kResolveThreads)
 k_exit_resolve(const Seg *__restrict__ oseg, uint32_t ntiles, uint32_t count,
                uint32_t *next, unsigned long long *ctr,
@@ -1246,12 +1248,10 @@ constexpr uint32_t kTableProbes = 512;
 
 // Insert (key, id) keeping the smallest id; reads before each atomic so that
 // the common case (key present with a smaller id) stays a plain load.
-// *at gets the key's slot when given.
 __device__ __forceinline__ bool table_insert(unsigned long long *keys,
                                              int32_t *vals, uint32_t mask,
                                              unsigned long long key,
-                                             int32_t id, unsigned *fresh,
-                                             uint32_t *at = nullptr) {
+                                             int32_t id, unsigned *fresh) {
   uint32_t h = (uint32_t)mix64(key) & mask;
 #pragma unroll 1
   for (uint32_t probe = 0; probe <= mask && probe < kTableProbes; ++probe) {
@@ -1266,7 +1266,6 @@ __device__ __forceinline__ bool table_insert(unsigned long long *keys,
     if (cur == key) {
       if (__atomic_load_n(&vals[h], __ATOMIC_RELAXED) > id)
         atomicMin(&vals[h], id);
-      if (at) *at = h;
       return true;
     }
     h = (h + 1) & mask;
@@ -1274,21 +1273,73 @@ __device__ __forceinline__ bool table_insert(unsigned long long *keys,
   return false;
 }
 
+// K insertions of one thread side by side: every step's loads are issued for
+// all of them before any is used, so K chains of dependent round trips (slot,
+// claim, value) cost about one.  Keys of kEmptyKey are no insertion.  at[k]
+// gets the slot of key k; false when some key found no room.
+template <int K>
+__device__ __forceinline__ bool table_insert_many(
+    unsigned long long *keys, int32_t *vals, uint32_t mask,
+    const unsigned long long (&key)[K], const int32_t (&id)[K],
+    uint32_t (&at)[K], unsigned *fresh) {
+  bool open[K], made[K], any = false, ok = true;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    at[k] = (uint32_t)mix64(key[k]) & mask;
+    open[k] = key[k] != kEmptyKey;
+    made[k] = false;
+    any |= open[k];
+  }
+#pragma unroll 1
+  for (uint32_t probe = 0; any; ++probe) {
+    if (probe > mask || probe == kTableProbes) {
+      ok = false;
+      break;
+    }
+    unsigned long long cur[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) cur[k] = load_dev64(&keys[at[k]]);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      made[k] = open[k] && cur[k] == kEmptyKey;
+      if (made[k]) cur[k] = atomicCAS(&keys[at[k]], kEmptyKey, key[k]);
+    }
+    any = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!open[k]) continue;
+      made[k] = made[k] && cur[k] == kEmptyKey;
+      if (made[k] || cur[k] == key[k]) {
+        *fresh += made[k];
+        open[k] = false;
+      } else {
+        at[k] = (at[k] + 1) & mask;
+        any = true;
+      }
+    }
+  }
+  int32_t v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = (int32_t)load_dev((uint32_t *)&vals[at[k]]);
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (key[k] != kEmptyKey && v[k] > id[k]) atomicMin(&vals[at[k]], id[k]);
+  return ok;
+}
+
 __device__ __forceinline__ unsigned long long pair_key(int32_t a, int32_t d) {
   return ((unsigned long long)(uint32_t)a << 32) | (uint32_t)d;
 }
 
 // Per-tile table of the distinct final (asc, desc) pairs: in smooth regions
-// a tile holds few, so the global insert and the cell lookup run once per
-// distinct pair.  Noise-dominated tiles hold thousands (a cell of pure noise
-// has about three vertices); once half the slots are taken the table accepts
-// no new pair, probes stay short, and the remaining vertices take the
-// per-vertex path.  Linear probing without deletion: a pair that is in the
-// table is found before any empty slot.  A lane consults the table only when
-// its column's pair changes from one z to the next (a repeated pair has a
-// larger id than the one already recorded), which in smooth regions is once
-// or twice per column; concurrent inserts of one pair meet in one slot
-// through the compare-and-swap.
+// a tile holds few, so the global insert runs once per distinct pair.  Linear
+// probing without deletion: a pair that is in the table is found before any
+// empty slot.  Once half the slots are taken the table accepts no new pair
+// (probes stay short) and the tile is left to the slab pass below.  A lane
+// consults the table only when its column's pair changes from one z to the
+// next (a repeated pair has a larger id than the one already recorded), which
+// in smooth regions is once or twice per column; concurrent inserts of one
+// pair meet in one slot through the compare-and-swap.
 constexpr int kPairSlots = 1024;
 constexpr unsigned kPairLimit = kPairSlots / 2;
 constexpr int kPairProbes = 16;
@@ -1341,8 +1392,18 @@ __device__ __forceinline__ int32_t table_lookup(
 // once the exits are linked: the number of pairs, then the slot of each in
 // the field's table.  The output pass then reads that byte instead of the
 // codes and needs no decoding; a tile with one pair needs no bytes at all.
-// Record 0 marks a tile that kept the per-vertex path.
+// Record 0 marks a tile with more pairs: each vertex's own slot in the field's
+// table stands in the ms output, where the output pass finds it.
 constexpr unsigned kCellIdx = 255;
+
+// Tiles with more extrema than this are not tried with the table of
+// kPairSlots: cells number two to four per extremum, and the extrema outside
+// the tile add theirs, so it would overflow (unless the tile holds no more
+// vertices than the table takes pairs, as in a plane: a noisy 800x600 one takes
+// 144 us this way and 200 in slabs).  The line is flat: between 32 and
+// 256 no measured workload moves by more than 2 %, while none at all costs
+// 37 % on Perlin noise (512^3: 1.67 ms against 2.29 with every tile in slabs).
+constexpr unsigned kPairExtrema = 96;
 
 template <class C>
 __device__ __forceinline__ uint32_t *cell_record(uint16_t *tlist,
@@ -1372,8 +1433,7 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<C>(), pair_waves<C>())))
 k_tile_pairs(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, unsigned long long *ctr,
-             uint32_t *tstat, uint32_t ntiles, const uint32_t *run,
-             uint16_t *tlist, uint32_t *cidx) {
+             uint32_t *tstat, uint16_t *tlist, uint32_t *cidx) {
   static_assert(C::TZ % 4 == 0, "four planes per index word");
   __shared__ Decode<C> s;
   __shared__ uint32_t s_fresh[C::kThreads / 64];
@@ -1382,99 +1442,119 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
   __shared__ uint16_t sdense[kPairSlots];
   __shared__ unsigned sfill;
   const int tid = threadIdx.x;
-  // The second pass (after an overflow) runs only when *run is set, over a
-  // smaller grid that strides through the tiles.
-  if (run && !*run) return;
-  for (uint32_t blk = blockIdx.x; blk < ntiles; blk += gridDim.x) {
-    const BlockTile bt = block_tile_at(fds, tfield, blk, ntiles);
-    if (!bt.fd.ms) continue;  // uniform over the block
-    const Geo &g = bt.fd.g;
-    const Tile t = tile_at<C>(g, bt.tile);
-    for (int i = tid; i < kPairSlots; i += C::kThreads) {
-      skey[i] = kEmptyKey;
-      sval[i] = INT32_MAX;
-    }
-    if (tid == 0) sfill = 0;
-    const int cx = tid % C::TX, cy = tid / C::TX;
-    const int gx = t.x0 + cx, gy = t.y0 + cy;
-    const bool col_in = gx < (int)g.X && gy < (int)g.Y;
-    int nz = (int)g.Z - t.z0;
-    nz = col_in ? (nz < C::TZ ? nz : C::TZ) : 0;
-    // Column offset within a plane; plane bases are uniform over the block.
-    const uint32_t col = (uint32_t)gx + g.X * (uint32_t)gy;
-    uint32_t code[C::TZ];
-  #pragma unroll
-    for (int lz = 0; lz < C::TZ; ++lz)
-      code[lz] = bt.fd.lp[code_word<C>(bt.gt, lz, tid)];
-    decode_setup<C>(s, bt.gt, seg, R, g, t);
+  const BlockTile bt = block_tile(fds, tfield);
+  if (!bt.fd.ms) return;  // uniform over the block
+  const Geo &g = bt.fd.g;
+  const Tile t = tile_at<C>(g, bt.tile);
+  uint32_t *const ts = tstat + 4 * (size_t)bt.gt;
+  const unsigned inside = min(C::TX, (int)g.X - t.x0) *
+                          min(C::TY, (int)g.Y - t.y0) *
+                          min(C::TZ, (int)g.Z - t.z0);
+  if (ts[0] + ts[1] > kPairExtrema && inside > kPairLimit) {
+    if (tid == 0) ts[2] = kTilePending;  // uniform over the block
+    return;
+  }
+  for (int i = tid; i < kPairSlots; i += C::kThreads) {
+    skey[i] = kEmptyKey;
+    sval[i] = INT32_MAX;
+  }
+  if (tid == 0) sfill = 0;
+  const int cx = tid % C::TX, cy = tid / C::TX;
+  const int gx = t.x0 + cx, gy = t.y0 + cy;
+  const bool col_in = gx < (int)g.X && gy < (int)g.Y;
+  int nz = (int)g.Z - t.z0;
+  nz = col_in ? (nz < C::TZ ? nz : C::TZ) : 0;
+  // Column offset within a plane; plane bases are uniform over the block.
+  const uint32_t col = (uint32_t)gx + g.X * (uint32_t)gy;
+  uint32_t code[C::TZ];
+#pragma unroll
+  for (int lz = 0; lz < C::TZ; ++lz)
+    code[lz] = bt.fd.lp[code_word<C>(bt.gt, lz, tid)];
+  decode_setup<C>(s, bt.gt, seg, R, g, t);
 
-    unsigned fresh = 0;
-    bool overflow = false, lost = false;
-    // Every run of equal pairs down a column finds its slot in the tile's
-    // table (two 16-bit slots per word).  Only the smallest id of each pair
-    // matters: a vertex whose pair equals that of the vertex below it
-    // (previous z of the column) or of the lane before it (a smaller id in
-    // the same plane) is not that smallest id and inserts nothing; the
-    // smallest one matches neither, so it is never skipped.
-    const bool first_lane = (tid & 63) == 0;
-    unsigned long long last = kEmptyKey;
-    int last_slot = -1;
-    uint32_t sp[C::TZ / 2];
-  #pragma unroll
-    for (int lz = 0; lz < C::TZ; ++lz) {
-      const bool in = lz < nz;
-      unsigned long long key = kEmptyKey;
-      if (in) {
-        // The final labels are written here, where the pass is bound by its
-        // arithmetic and the stores overlap it; the output pass then writes
-        // only the cell ids.
-        const int32_t a = decode_final<C>(s, code[lz] & 0xffffu, false);
-        const int32_t d = decode_final<C>(s, code[lz] >> 16, true);
-        // Only the labels the caller wants (block-uniform tests).
-        if (bt.fd.A) plane_ptr(bt.fd.A, g, t.z0 + lz)[col] = a;
-        if (bt.fd.D) plane_ptr(bt.fd.D, g, t.z0 + lz)[col] = d;
-        key = pair_key(a, d);
-      }
-      if (in && key != last) {
-        last_slot = pair_slot(skey, &sfill, key, sdense);
-        lost |= last_slot < 0;
-      }
-      const unsigned long long left = __shfl_up(key, 1);
-      const bool repeat = key == last || (!first_lane && key == left);
-      last = key;
-      const uint32_t s16 = (uint32_t)last_slot & 0xffffu;
-      sp[lz / 2] = (lz & 1) ? (sp[lz / 2] | (s16 << 16)) : s16;
-      if (!repeat && in) {
-        const int32_t id = (int32_t)(col + g.XY * (uint32_t)(t.z0 + lz));
-        if (last_slot >= 0)
-          atomicMin(&sval[last_slot], id);
-        else if (!table_insert(bt.fd.keys, bt.fd.vals, bt.fd.mask, key, id,
-                               &fresh))
-          overflow = true;
-      }
+  bool lost = false;
+  // Every run of equal pairs down a column finds its slot in the tile's
+  // table (two 16-bit slots per word).  Only the smallest id of each pair
+  // matters: a vertex whose pair equals that of the vertex below it
+  // (previous z of the column) or of the lane before it (a smaller id in
+  // the same plane) is not that smallest id and inserts nothing; the
+  // smallest one matches neither, so it is never skipped.
+  const bool first_lane = (tid & 63) == 0;
+  unsigned long long last = kEmptyKey;
+  int last_slot = -1;
+  uint32_t sp[C::TZ / 2];
+#pragma unroll
+  for (int lz = 0; lz < C::TZ; ++lz) {
+    const bool in = lz < nz;
+    unsigned long long key = kEmptyKey;
+    if (in) {
+      // The final labels are written here, where the pass is bound by its
+      // arithmetic and the stores overlap it; the output pass then writes
+      // only the cell ids.
+      const int32_t a = decode_final<C>(s, code[lz] & 0xffffu, false);
+      const int32_t d = decode_final<C>(s, code[lz] >> 16, true);
+      // Only the labels the caller wants (block-uniform tests).
+      if (bt.fd.A) plane_ptr(bt.fd.A, g, t.z0 + lz)[col] = a;
+      if (bt.fd.D) plane_ptr(bt.fd.D, g, t.z0 + lz)[col] = d;
+      key = pair_key(a, d);
     }
-    // Block-uniform from here: the tile keeps the byte path when every
-    // vertex found a slot and few enough pairs were claimed.
-    const bool any_lost = __syncthreads_or(lost);
-    const unsigned n = sfill;
-    const bool indexed = !any_lost && n <= kCellIdx;
-    uint32_t *rec = cell_record<C>(tlist, bt.gt);
-    for (int i = tid; i < kPairSlots; i += C::kThreads) {
-      if (skey[i] != kEmptyKey) {
-        uint32_t at = 0;
-        if (!table_insert(bt.fd.keys, bt.fd.vals, bt.fd.mask, skey[i], sval[i],
-                          &fresh, &at))
-          overflow = true;
-        else if (indexed)
-          rec[1 + sdense[i]] = at;
-      }
+    if (in && key != last) {
+      last_slot = pair_slot(skey, &sfill, key, sdense);
+      lost |= last_slot < 0;
     }
-    if (tid == 0) rec[0] = indexed ? n : 0u;
-    if (indexed && n > 1) {
-  #pragma unroll
+    const unsigned long long left = __shfl_up(key, 1);
+    const bool repeat = key == last || (!first_lane && key == left);
+    last = key;
+    const uint32_t s16 = (uint32_t)last_slot & 0xffffu;
+    sp[lz / 2] = (lz & 1) ? (sp[lz / 2] | (s16 << 16)) : s16;
+    if (!repeat && in && last_slot >= 0)
+      atomicMin(&sval[last_slot],
+                (int32_t)(col + g.XY * (uint32_t)(t.z0 + lz)));
+  }
+  // Block-uniform from here: a tile some vertex of which found no slot goes
+  // to the slab pass whole.
+  if (__syncthreads_or(lost)) {
+    if (tid == 0) ts[2] = kTilePending;
+    return;
+  }
+  const unsigned n = sfill;
+  const bool indexed = n <= kCellIdx;
+  uint32_t *rec = cell_record<C>(tlist, bt.gt);
+  unsigned fresh = 0;
+  bool overflow = false;
+  {
+    constexpr int K = (kPairSlots + C::kThreads - 1) / C::kThreads;
+    unsigned long long key[K];
+    int32_t id[K];
+    uint32_t at[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = tid + k * C::kThreads;
+      key[k] = skey[i];
+      id[k] = sval[i];
+    }
+    overflow = !table_insert_many<K>(bt.fd.keys, bt.fd.vals, bt.fd.mask, key,
+                                     id, at, &fresh);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = tid + k * C::kThreads;
+      if (key[k] == kEmptyKey) continue;
+      if (indexed) rec[1 + sdense[i]] = at[k];
+      else sval[i] = (int32_t)at[k];  // the pair's slot, for its vertices
+    }
+  }
+  if (tid == 0) rec[0] = indexed ? n : 0u;
+  // New pairs this tile inserted: summed per tile, folded per field later.
+  for (int o = 32; o > 0; o >>= 1) fresh += __shfl_xor(fresh, o);
+  if ((tid & 63) == 0) s_fresh[tid >> 6] = fresh;
+  if (overflow) atomicOr(ctr + kCtrOverflow, kOverflowFirst);
+  __syncthreads();
+  if (indexed) {
+    if (n > 1) {
+#pragma unroll
       for (int j = 0; j < C::TZ / 4; ++j) {
         uint32_t w = 0;
-  #pragma unroll
+#pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int lz = 4 * j + b;
           const uint32_t sl = (sp[lz / 2] >> (16 * (lz & 1))) & 0xffffu;
@@ -1483,17 +1563,141 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
         cidx[cell_word<C>(bt.gt, j, tid)] = w;
       }
     }
-    // New pairs this tile inserted: summed per tile, folded per field later.
-    for (int o = 32; o > 0; o >>= 1) fresh += __shfl_xor(fresh, o);
-    if ((tid & 63) == 0) s_fresh[tid >> 6] = fresh;
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t c = 0;
-      for (int w = 0; w < C::kThreads / 64; ++w) c += s_fresh[w];
-      tstat[4 * (size_t)bt.gt + 2] = c;
+  } else {
+#pragma unroll
+    for (int lz = 0; lz < C::TZ; ++lz)
+      if (lz < nz)
+        plane_ptr(bt.fd.ms, g, t.z0 + lz)[col] =
+            sval[(sp[lz / 2] >> (16 * (lz & 1))) & 0xffffu];
+  }
+  if (tid == 0) {
+    uint32_t c = 0;
+    for (int w = 0; w < C::kThreads / 64; ++w) c += s_fresh[w];
+    ts[2] = c;
+  }
+}
+
+// The tiles the pair pass left out, where most vertices carry a pair of their
+// own (in pure noise a cell has about three).  A tile is taken in slabs of
+// kSlabZ planes, one block each: a slab has as many slots as vertices, so its
+// table never overflows, every global insert happens in the flush, kSlabZ per
+// thread side by side, and a field of few tiles still fills the chip.  Each
+// vertex's slot in the field's table goes to the ms output.  What bounds it is
+// the latency of those round trips on small fields and the rate of random
+// atomics on large ones.  With one thread inserting, and later looking up, its
+// 16 vertices in turn, a 64^3 field's 32 tiles took 86 us in the pair pass and
+// 64 us in the output pass, 64 fields of 32..256 1.11 and 0.57 ms; now pairs,
+// slabs and output take 34 + 22 + 9 us and 0.34 + 0.38 + 0.25 ms.
+//
+// The grid strides over the slabs; each wave reads the marks of 64 of its
+// block's slabs at once.  The second launch (`again`) does nothing unless the
+// first table overflowed, and then takes every tile.
+constexpr int kSlabZ = 4;
+// Three resident blocks per CU, twice over; odd, so that a block's slabs come
+// from every depth of the tiles (thin fields fill only the lowest).
+constexpr unsigned kSlabBlocks = 1535;
+
+template <class C>
+__global__ void __launch_bounds__(C::kThreads)
+k_tile_slabs(const FieldDev *__restrict__ fds,
+             const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
+             const uint32_t *__restrict__ R, unsigned long long *ctr,
+             uint32_t *tstat, uint32_t ntiles, bool again, uint16_t *tlist) {
+  constexpr int T = C::kThreads, NS = C::TZ / kSlabZ, SLOTS = kSlabZ * T;
+  static_assert(C::TZ % kSlabZ == 0 && (SLOTS & (SLOTS - 1)) == 0, "slabs");
+  __shared__ Decode<C> s;
+  __shared__ unsigned long long skey[SLOTS];
+  __shared__ int32_t sval[SLOTS];
+  __shared__ uint32_t s_fresh;
+  const int tid = threadIdx.x;
+  if (again && !(ctr[kCtrOverflow] & kOverflowFirst)) return;
+  const uint64_t units = (uint64_t)ntiles * NS;  // slabs of all tiles
+  for (uint64_t u0 = blockIdx.x; u0 < units; u0 += 64ull * gridDim.x) {
+    const uint64_t ul = u0 + (uint64_t)(tid & 63) * gridDim.x;
+    unsigned long long todo = __ballot(
+        ul < units && (again || (tstat[4 * (ul / NS) + 2] & kTilePending)));
+    for (; todo; todo &= todo - 1) {
+      const uint64_t u =
+          u0 + (uint64_t)(__ffsll((long long)todo) - 1) * gridDim.x;
+      const uint32_t slab = (uint32_t)(u % NS);
+      const int z0 = (int)slab * kSlabZ;  // first plane within the tile
+      BlockTile bt;
+      bt.gt = (uint32_t)(u / NS);
+      bt.fi = tfield[bt.gt];
+      bt.fd = fds[bt.fi];
+      bt.tile = bt.gt - bt.fd.tile0;
+      if (!bt.fd.ms) continue;  // uniform over the block
+      const Geo &g = bt.fd.g;
+      const Tile t = tile_at<C>(g, bt.tile);
+      if (t.z0 + z0 >= (int)g.Z) continue;  // no plane of the domain in it
+#pragma unroll
+      for (int k = 0; k < kSlabZ; ++k) {
+        skey[tid + k * T] = kEmptyKey;
+        sval[tid + k * T] = INT32_MAX;
+      }
+      if (tid == 0) s_fresh = 0;
+      const int gx = t.x0 + tid % C::TX, gy = t.y0 + tid / C::TX;
+      int nz = (int)g.Z - (t.z0 + z0);
+      nz = gx < (int)g.X && gy < (int)g.Y ? (nz < kSlabZ ? nz : kSlabZ) : 0;
+      const uint32_t col = (uint32_t)gx + g.X * (uint32_t)gy;
+      uint32_t code[kSlabZ];
+#pragma unroll
+      for (int k = 0; k < kSlabZ; ++k)
+        code[k] = bt.fd.lp[code_word<C>(bt.gt, z0 + k, tid)];
+      decode_setup<C>(s, bt.gt, seg, R, g, t);
+      uint32_t slot[kSlabZ];
+#pragma unroll
+      for (int k = 0; k < kSlabZ; ++k) {
+        if (k >= nz) continue;
+        const int32_t a = decode_final<C>(s, code[k] & 0xffffu, false);
+        const int32_t d = decode_final<C>(s, code[k] >> 16, true);
+        if (bt.fd.A) plane_ptr(bt.fd.A, g, t.z0 + z0 + k)[col] = a;
+        if (bt.fd.D) plane_ptr(bt.fd.D, g, t.z0 + z0 + k)[col] = d;
+        const unsigned long long key = pair_key(a, d);
+        // As many slots as vertices: the pair or an empty slot is found.
+        uint32_t h = ((uint32_t)a * 0x9e3779b1u + (uint32_t)d * 0x85ebca6bu) /
+                     (uint32_t)((1ull << 32) / SLOTS);
+        for (;;) {
+          unsigned long long cur = skey[h];
+          if (cur == kEmptyKey) {
+            cur = atomicCAS(&skey[h], kEmptyKey, key);
+            if (cur == kEmptyKey) break;
+          }
+          if (cur == key) break;
+          h = (h + 1) & (SLOTS - 1);
+        }
+        atomicMin(&sval[h], (int32_t)(col + g.XY * (uint32_t)(t.z0 + z0 + k)));
+        slot[k] = h;
+      }
+      __syncthreads();
+      unsigned fresh = 0;
+      {
+        unsigned long long key[kSlabZ];
+        int32_t id[kSlabZ];
+        uint32_t at[kSlabZ];
+#pragma unroll
+        for (int k = 0; k < kSlabZ; ++k) {
+          key[k] = skey[tid + k * T];
+          id[k] = sval[tid + k * T];
+        }
+        if (!table_insert_many<kSlabZ>(bt.fd.keys, bt.fd.vals, bt.fd.mask, key,
+                                       id, at, &fresh))
+          atomicOr(ctr + kCtrOverflow, again ? kOverflowFull : kOverflowFirst);
+#pragma unroll
+        for (int k = 0; k < kSlabZ; ++k) sval[tid + k * T] = (int32_t)at[k];
+      }
+      for (int o = 32; o > 0; o >>= 1) fresh += __shfl_xor(fresh, o);
+      if ((tid & 63) == 0 && fresh) atomicAdd(&s_fresh, fresh);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kSlabZ; ++k)
+        if (k < nz) plane_ptr(bt.fd.ms, g, t.z0 + z0 + k)[col] = sval[slot[k]];
+      if (tid == 0) {
+        if (s_fresh) atomicAdd(&tstat[4 * (size_t)bt.gt + 2], s_fresh);
+        if (slab == 0) cell_record<C>(tlist, bt.gt)[0] = 0;
+      }
+      __syncthreads();  // the LDS tables are cleared for the next tile
     }
-    if (overflow) atomicOr(ctr + kCtrOverflow, 1ull);
-    __syncthreads();  // the LDS tables are cleared for the next tile
   }
 }
 
@@ -1504,9 +1708,7 @@ k_tile_write(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ R, uint16_t *tlist,
              const uint32_t *__restrict__ cidx) {
   __shared__ Decode<C> s;
-  __shared__ unsigned long long skey[kPairSlots];
-  __shared__ int32_t scell[kPairSlots];
-  __shared__ unsigned sfill;
+  __shared__ int32_t scell[kCellIdx + 1];
   static_assert(kCellIdx <= (unsigned)C::kThreads, "a slot per thread");
   const int tid = threadIdx.x;
   // The tile's cell record needs only the tile index, so its count and
@@ -1519,9 +1721,7 @@ k_tile_write(const FieldDev *__restrict__ fds,
   const uint32_t rk = rec[1 + ((unsigned)tid < kCellIdx ? tid : 0)];
   const BlockTile bt = block_tile(fds, tfield);
   const Geo &g = bt.fd.g;
-  int32_t *__restrict__ A = bt.fd.A;
-  int32_t *__restrict__ D = bt.fd.D;
-  int32_t *__restrict__ ms = bt.fd.ms;
+  int32_t *const ms = bt.fd.ms;
   const Tile t = tile_at<C>(g, bt.tile);
   const int cx = tid % C::TX, cy = tid / C::TX;
   const int gx = t.x0 + cx, gy = t.y0 + cy;
@@ -1548,58 +1748,38 @@ k_tile_write(const FieldDev *__restrict__ fds,
             scell[(w[lz / 4] >> (8 * (lz % 4))) & 0xffu];
     return;
   }
-  if (ms) {  // uniform over the block: ms belongs to the field
-    for (int i = tid; i < kPairSlots; i += C::kThreads) skey[i] = kEmptyKey;
+  if (ms) {
+    // Each vertex's slot in the field's table stands in ms: all of a
+    // column's slots, then all of its cell ids, then the stores (planes past
+    // the column read vertex 0's entry and slot 0, and are not used).
+    uint32_t sl[C::TZ];
+#pragma unroll
+    for (int lz = 0; lz < C::TZ; ++lz)
+      sl[lz] = (uint32_t)plane_ptr(ms, g, lz < nz ? t.z0 + lz : 0)[lz < nz ? col : 0u];
+    int32_t cell[C::TZ];
+#pragma unroll
+    for (int lz = 0; lz < C::TZ; ++lz)
+      cell[lz] = bt.fd.vals[lz < nz ? sl[lz] & bt.fd.mask : 0u];
+#pragma unroll
+    for (int lz = 0; lz < C::TZ; ++lz)
+      if (lz < nz) plane_ptr(ms, g, t.z0 + lz)[col] = cell[lz];
+    return;
   }
-  if (tid == 0) sfill = 0;
+  // No cells wanted: the labels are decoded and written here.
+  int32_t *__restrict__ A = bt.fd.A;
+  int32_t *__restrict__ D = bt.fd.D;
   uint32_t code[C::TZ];
 #pragma unroll
   for (int lz = 0; lz < C::TZ; ++lz)
     code[lz] = bt.fd.lp[code_word<C>(bt.gt, lz, tid)];
   decode_setup<C>(s, bt.gt, seg, R, g, t);
-
-  int16_t slot[C::TZ];
-  // The slot (or, off the table, the cell) of the column's previous pair.
-  unsigned long long last = kEmptyKey;
-  int last_slot = -1;
-  int32_t last_cell = -1;
 #pragma unroll
   for (int lz = 0; lz < C::TZ; ++lz) {
-    const bool in = lz < nz;
-    int32_t a = 0, d = 0;
-    if (in) {
-      a = decode_final<C>(s, code[lz] & 0xffffu, false);
-      d = decode_final<C>(s, code[lz] >> 16, true);
-      if (!ms) {  // with cells, the pair pass has written the labels
-        if (A) plane_ptr(A, g, t.z0 + lz)[col] = a;
-        if (D) plane_ptr(D, g, t.z0 + lz)[col] = d;
-      }
-    }
-    slot[lz] = -1;
-    if (ms) {  // uniform over the block: ms belongs to the field
-      const unsigned long long key = pair_key(a, d);
-      if (in && key != last) {
-        last = key;
-        last_slot = pair_slot(skey, &sfill, key);
-        if (last_slot < 0)  // not in the tile's table: look this pair up alone
-          last_cell = table_lookup(bt.fd.keys, bt.fd.vals, bt.fd.mask, key);
-      }
-      if (in) {
-        slot[lz] = (int16_t)last_slot;
-        if (last_slot < 0) plane_ptr(ms, g, t.z0 + lz)[col] = last_cell;
-      }
-    }
-  }
-  if (!ms) return;  // uniform over the block: ms belongs to the field
-  __syncthreads();
-  for (int i = tid; i < kPairSlots; i += C::kThreads)
-    if (skey[i] != kEmptyKey)
-      scell[i] = table_lookup(bt.fd.keys, bt.fd.vals, bt.fd.mask, skey[i]);
-  __syncthreads();
-#pragma unroll
-  for (int lz = 0; lz < C::TZ; ++lz) {
-    if (lz < nz && slot[lz] >= 0)
-      plane_ptr(ms, g, t.z0 + lz)[col] = scell[slot[lz]];
+    if (lz >= nz) continue;
+    const int32_t a = decode_final<C>(s, code[lz] & 0xffffu, false);
+    const int32_t d = decode_final<C>(s, code[lz] >> 16, true);
+    if (A) plane_ptr(A, g, t.z0 + lz)[col] = a;
+    if (D) plane_ptr(D, g, t.z0 + lz)[col] = d;
   }
 }
 
@@ -1685,53 +1865,40 @@ k_call_setup(const FieldDev *__restrict__ fds, int nfields, uint32_t nt,
   }
 }
 
-// Table capacity of every field that wants cells, chosen on the device from
-// its extremum counts: the first capacity (`regrow` == 0), or, when the pair
-// pass overflowed (`regrow` != 0), the capacity that always suffices, with
-// the field's cell counter cleared for the second pass.  *run tells the
-// passes that follow whether they have work.  The host reserved each
-// field's region for the largest capacity its vertex count allows.
-__global__ void __launch_bounds__(kBlock)
-k_table_plan(FieldDev *fds, int nfields, unsigned long long *fctr,
-             unsigned long long *ctr, uint64_t requested, int regrow,
-             uint32_t *run) {
-  const bool again = regrow && (ctr[kCtrOverflow] & 1ull);
-  for (int i = threadIdx.x; i < nfields; i += kBlock) {
-    if (!fds[i].ms) continue;
-    const uint64_t n = fds[i].g.N;
-    const unsigned long long *fc = fctr + (size_t)i * kFieldCtrs;
-    if (!regrow) {
-      fds[i].mask = (uint32_t)(
-          table_first_capacity(n, fc[kFMaxima], fc[kFMinima], requested) - 1);
-    } else if (again) {
-      fds[i].mask = (uint32_t)(table_capacity(n, fc[kFMaxima], fc[kFMinima]) - 1);
-      fctr[(size_t)i * kFieldCtrs + kFCells] = 0;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    *run = regrow ? (again ? 1u : 0u) : 1u;
-    if (again) ctr[kCtrOverflow] &= ~1ull;
-  }
-}
-
-// Clear the tables of the fields that want cells (capacities from the
-// plan), over a fixed grid; nothing to do when *run is 0.
+// Chooses the pair table capacity of every field that wants cells, on the
+// device from its extremum counts, and clears the tables over a fixed grid:
+// the first capacity, or (`regrow`), when the first pair pass overflowed, the
+// capacity that always suffices, with the tiles' cell counters cleared for the
+// second pass; without an overflow there is nothing to do then.  The host
+// reserved each field's region for the largest capacity its vertex count
+// allows.  Every block works the capacities out for itself (a launch of its
+// own for them costs 4 us); the first one records them.
 constexpr unsigned kClearBlocks = 2048;
 
 __global__ void __launch_bounds__(kBlock)
-k_table_clear_all(const FieldDev *__restrict__ fds, int nfields,
-                  const uint32_t *__restrict__ run) {
-  if (!*run) return;
+k_table_clear_all(FieldDev *fds, int nfields,
+                  const unsigned long long *__restrict__ fctr,
+                  const unsigned long long *__restrict__ ctr,
+                  uint64_t requested, bool regrow, uint32_t *tstat,
+                  uint32_t nt) {
+  if (regrow && !(ctr[kCtrOverflow] & kOverflowFirst)) return;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+  const uint64_t k0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (regrow)
+    for (uint64_t k = k0; k < nt; k += stride) tstat[4 * k + 2] = 0;
   for (int i = 0; i < nfields; ++i) {
-    const FieldDev fd = fds[i];
-    if (!fd.ms) continue;
-    const uint64_t cap = (uint64_t)fd.mask + 1;
-    for (uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x; k < cap;
-         k += stride) {
-      fd.keys[k] = kEmptyKey;
-      fd.vals[k] = INT32_MAX;
+    if (!fds[i].ms) continue;
+    unsigned long long *const keys = fds[i].keys;
+    int32_t *const vals = fds[i].vals;
+    const uint64_t n = fds[i].g.N;
+    const unsigned long long *fc = fctr + (size_t)i * kFieldCtrs;
+    const uint64_t cap =
+        regrow ? table_capacity(n, fc[kFMaxima], fc[kFMinima])
+               : table_first_capacity(n, fc[kFMaxima], fc[kFMinima], requested);
+    if (k0 == 0) fds[i].mask = (uint32_t)(cap - 1);
+    for (uint64_t k = k0; k < cap; k += stride) {
+      keys[k] = kEmptyKey;
+      vals[k] = INT32_MAX;
     }
   }
 }
@@ -1992,7 +2159,6 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
   unsigned long long *rstat = cv.take<unsigned long long>(4ull * nt);
   uint16_t *tlist = cv.take<uint16_t>(2ull * C::kHalo * nt);
   uint32_t *xs = cv.take<uint32_t>(2ull * C::TY * C::TZ * nt);
-  uint32_t *run = cv.take<uint32_t>(1);
   uint32_t *cidx = any_ms ? cv.take<uint32_t>((size_t)nt * C::kThreads *
                                                (C::TZ / 4))
                           : nullptr;
@@ -2045,20 +2211,22 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
     // pass and its clear return at once when nothing overflowed).
     const unsigned cb = (unsigned)std::min<uint64_t>(
         kClearBlocks, (tab_slots + kBlock - 1) / kBlock);
-    k_table_plan<<<1, kBlock, 0, s>>>(fds, nfields, fctr, ctr,
-                                      ctx->table_first, 0, run);
     MSC_PHASE(ctx, s, "table_clear", 12.0 * total_n,
-              (k_table_clear_all<<<cb, kBlock, 0, s>>>(fds, nfields, run)));
+              (k_table_clear_all<<<cb, kBlock, 0, s>>>(
+                  fds, nfields, fctr, ctr, ctx->table_first, false, tstat,
+                  nt)));
     MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
               (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
-                  fds, tfield, seg, next, ctr, tstat, nt, nullptr, tlist,
-                  cidx)));
-    k_table_plan<<<1, kBlock, 0, s>>>(fds, nfields, fctr, ctr,
-                                      ctx->table_first, 1, run);
-    k_table_clear_all<<<cb, kBlock, 0, s>>>(fds, nfields, run);
-    const unsigned rb = nt < 4096u ? nt : 4096u;
-    k_tile_pairs<C><<<rb, C::kThreads, 0, s>>>(fds, tfield, seg, next, ctr,
-                                               tstat, nt, run, tlist, cidx);
+                  fds, tfield, seg, next, ctr, tstat, tlist, cidx)));
+    const unsigned sb =
+        std::min<uint64_t>((uint64_t)nt * (C::TZ / kSlabZ), kSlabBlocks);
+    MSC_PHASE(ctx, s, "tile_slabs", 0.0,
+              (k_tile_slabs<C><<<sb, C::kThreads, 0, s>>>(
+                  fds, tfield, seg, next, ctr, tstat, nt, false, tlist)));
+    k_table_clear_all<<<cb, kBlock, 0, s>>>(fds, nfields, fctr, ctr,
+                                            ctx->table_first, true, tstat, nt);
+    k_tile_slabs<C><<<sb, C::kThreads, 0, s>>>(fds, tfield, seg, next, ctr,
+                                               tstat, nt, true, tlist);
     MSC_HIP_TRY(hipGetLastError());
     k_tile_stat_reduce<<<grid_for(nt), kBlock, 0, s>>>(tstat, 2, nt, tfield,
                                                        fctr, kFCells);

@@ -288,3 +288,33 @@ def test_output_pass_paths_in_one_call(msc):
         ref = O.segment(fld)
         for name, g, w in zip(("asc", "desc", "ms"), out, ref):
             np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=name)
+
+
+@pytest.mark.parametrize("dims", [(33, 17, 5), (32, 16, 16), (31, 15, 4),
+                                  (70, 33, 21), (64, 48, 17)])
+@pytest.mark.parametrize("kind", [0.1, 0.2, 0.3, 0.45, "noise"])
+def test_cell_passes(msc, dims, kind):
+    """Fields whose tiles hold from a few cells to thousands, so that they
+    take the byte record, the slots of one tile's table, and the slab pass,
+    at slab and tile remainders; every tile shape, cells alone and with the
+    labels, and (capacity 1024) a table that overflows."""
+    if kind == "noise":
+        f = synth.random_field(dims, seed=5)
+    else:
+        f = synth.perlin_field(dims, seed=5, frequency=kind)
+    want = O.segment(f)
+    try:
+        for shape in msc.tile_shapes():
+            msc.set_tile(*shape)
+            for cap in (0, 1024):
+                msc.set_table_capacity(cap)
+                got = gpu_segment(msc, f)
+                for name, g, w in zip(("asc", "desc", "ms"), got, want):
+                    np.testing.assert_array_equal(
+                        g, w, err_msg=f"{shape} {cap} {name}")
+                assert msc.last_stats()["n_cells"] == np.unique(want[2]).size
+            got = gpu_segment(msc, f, want=("ms",))
+            np.testing.assert_array_equal(got[2], want[2], err_msg=f"{shape}")
+    finally:
+        msc.set_table_capacity(0)
+        msc.set_tile(*msc.tile_shapes()[0])
