@@ -36,7 +36,7 @@ int reserve(msc_ctx *ctx, DevBuf &buf, size_t bytes) {
   if (bytes <= buf.bytes) return MSC_OK;
   if (buf.external) return MSC_ENOMEM;
   // The old block may still be read by this context's queued work.
-  if (ctx->done_valid) MSC_TRY(host_wait(ctx, ctx->done));
+  if (ctx->done_valid) MSC_TRY(host_wait(ctx, ctx->last_done));
   ++ctx->grows;
   if (buf.ptr) {
     MSC_HIP_TRY(hipFree(buf.ptr));
@@ -73,12 +73,13 @@ int clear_counters(msc_ctx *ctx, hipStream_t stream) {
 
 int begin_call(msc_ctx *ctx, hipStream_t s) {
   if (ctx->done_valid && ctx->last_stream != s)
-    MSC_HIP_TRY(hipStreamWaitEvent(s, ctx->done, 0));
+    MSC_HIP_TRY(hipStreamWaitEvent(s, ctx->last_done, 0));
   return MSC_OK;
 }
 
-int end_call(msc_ctx *ctx, hipStream_t s) {
-  MSC_HIP_TRY(hipEventRecord(ctx->done, s));
+int end_call(msc_ctx *ctx, hipStream_t s, hipEvent_t recorded) {
+  if (!recorded) MSC_HIP_TRY(hipEventRecord(ctx->done, s));
+  ctx->last_done = recorded ? recorded : ctx->done;
   ctx->last_stream = s;
   ctx->done_valid = true;
   return MSC_OK;
@@ -263,7 +264,7 @@ int msc_set_workspace(msc_ctx *ctx, void *ptr, size_t bytes) {
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
   // The current workspace may still be read by queued work.
-  if (ctx->done_valid) MSC_HIP_TRY(hipEventSynchronize(ctx->done));
+  if (ctx->done_valid) MSC_HIP_TRY(hipEventSynchronize(ctx->last_done));
   if (ctx->ws.ptr && !ctx->ws.external) MSC_HIP_TRY(hipFree(ctx->ws.ptr));
   ctx->ws = msc::DevBuf{};
   if (ptr) {

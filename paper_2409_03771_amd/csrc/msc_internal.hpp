@@ -141,6 +141,8 @@ struct CallRec {
   bool pending = false;                 // issued; its event not yet waited on
   unsigned long long *hctr = nullptr;   // pinned copy of the counter block
   unsigned long long *hfctr = nullptr;  // pinned per-field counters
+  unsigned long long *dhctr = nullptr, *dhfctr = nullptr;  // as the device
+                                        // addresses them
   size_t hfctr_cap = 0;                 // entries
   int nfields = 0;
   std::vector<int64_t> n;               // vertices per field
@@ -173,6 +175,7 @@ struct msc_ctx {
   // waits for it (the workspaces are shared), and the stats calls wait for
   // it before reading the counters.
   hipEvent_t done = nullptr;
+  hipEvent_t last_done = nullptr;  // `done`, or the last call record's event
   hipStream_t last_stream = nullptr;
   bool done_valid = false;
   msc::PinnedSlot slots[msc::kPinnedSlots];
@@ -204,7 +207,8 @@ int host_wait(msc_ctx *ctx, hipEvent_t e);
 // Order a call on stream `s` after the context's previous call (which may
 // have run on another stream), and mark the end of a call's work.
 int begin_call(msc_ctx *ctx, hipStream_t s);
-int end_call(msc_ctx *ctx, hipStream_t s);
+// (`recorded`: an event of the call's own, already recorded after its work.)
+int end_call(msc_ctx *ctx, hipStream_t s, hipEvent_t recorded = nullptr);
 
 // A pinned host buffer of at least `bytes` for one host-to-device copy on
 // `s`; call slot_copied after issuing the copy.

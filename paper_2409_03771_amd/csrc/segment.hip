@@ -38,6 +38,7 @@
 #include <climits>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "msc_internal.hpp"
@@ -93,6 +94,16 @@ struct FieldDev {
                                // ghost vertices (fixed points, Alg. 1)
   Geo g;
 };
+
+// Calls of at most this many tiles fold their counters with one atomic per
+// tile where the count is made, and resolve their exits without an order: most
+// of those blocks are resident at once, and the same-address atomics (10 ns
+// each) end within the kernels.  Larger calls fold per-tile records in kernels
+// of their own and sort the tiles.  Each launch costs 3 to 5 us: with the line
+// at 512 instead of 4,096, 200^3 takes 184 us instead of 164 and 90 fields of
+// 30..100 take 480 us instead of 438; at 20,000, Perlin noise at 512^3 (16,384
+// tiles) takes 1.67 ms instead of 1.63.
+constexpr uint32_t kDirectTiles = 4096;
 
 // A tile's exits in the list: `base`, then `na` ascent exits and `nd`
 // descent exits, each group in increasing halo-index order.
@@ -320,6 +331,7 @@ struct ExitOut {
                        // exit, ascent exits first (numbers are tile-local)
   uint32_t *xs;        // per global tile: the codes of its first and last
                        // x columns (shell_word)
+  bool direct;         // counters also go to the fields' (kDirectTiles)
 };
 
 // Counters are summed per block and written per tile, then folded by these
@@ -344,34 +356,54 @@ __device__ __forceinline__ void fold_stat(bool in, uint32_t v, uint32_t fi,
   }
 }
 
+// The same over a block of NW waves, with one atomic per block when its tiles
+// share a field.  `tmp` holds NW words of LDS.
+template <int NW>
+__device__ __forceinline__ void fold_stat_block(bool in, uint32_t v,
+                                                uint32_t fi, bool uniform,
+                                                uint32_t *tmp,
+                                                unsigned long long *fctr,
+                                                int which) {
+  if (!uniform) {
+    fold_stat(in, v, fi, fctr, which);
+    return;
+  }
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t sum = 0;
+    for (int w = 0; w < NW; ++w) sum += tmp[w];
+    if (sum)
+      atomicAdd(fctr + (size_t)fi * kFieldCtrs + which, (unsigned long long)sum);
+  }
+  __syncthreads();
+}
+
 // Marks, in a tile's cell counter, a tile that the pair pass left to the slab
 // pass (the counter itself stays below it).
 constexpr uint32_t kTilePending = 0x80000000u;
 
-__global__ void __launch_bounds__(kBlock)
-k_tile_stat_reduce(const uint32_t *__restrict__ tstat, int k, uint32_t nt,
-                   const uint32_t *__restrict__ tfield,
-                   unsigned long long *fctr, int which) {
-  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-  const bool in = i < nt;
-  const uint32_t v = in ? tstat[4 * (size_t)i + k] & ~kTilePending : 0u;
-  const uint32_t fi = in ? tfield[i] : 0u;
-  fold_stat(in, v, fi, fctr, which);
+// The kernels that read a word per tile run 1024-thread blocks and fold per
+// block in LDS first: tile means crowd into a few buckets, and global atomics
+// on one address serialise across the chip.
+constexpr int kOrderBlock = 1024;
+
+inline unsigned order_grid(uint32_t n) {
+  return (n + kOrderBlock - 1) / kOrderBlock;
 }
 
-// Maxima, minima and exits of every tile in one pass (tile counters 0, 1
-// and 3).
-__global__ void __launch_bounds__(kBlock)
-k_tile_stats3(const uint32_t *__restrict__ tstat, uint32_t nt,
-              const uint32_t *__restrict__ tfield, unsigned long long *fctr) {
-  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+// New cells of every tile (tile counter 2) into their fields'.
+__global__ void __launch_bounds__(kOrderBlock)
+k_tile_cells(const uint32_t *__restrict__ tstat, uint32_t nt,
+             const uint32_t *__restrict__ tfield, unsigned long long *fctr) {
+  __shared__ uint32_t tmp[kOrderBlock / 64];
+  const uint32_t i0 = blockIdx.x * kOrderBlock, i = i0 + threadIdx.x;
   const bool in = i < nt;
-  const uint4 c = in ? reinterpret_cast<const uint4 *>(tstat)[i]
-                     : make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t v = in ? tstat[4 * (size_t)i + 2] & ~kTilePending : 0u;
   const uint32_t fi = in ? tfield[i] : 0u;
-  fold_stat(in, c.x, fi, fctr, kFMaxima);
-  fold_stat(in, c.y, fi, fctr, kFMinima);
-  fold_stat(in, c.w, fi, fctr, kFExits);
+  const bool uniform = !__syncthreads_or(in && fi != tfield[i0]);
+  fold_stat_block<kOrderBlock / 64>(in, v, fi, uniform, tmp, fctr, kFCells);
 }
 
 // Per-block (longest chain, links followed) of the exit resolution into the
@@ -642,6 +674,8 @@ k_tile_local(const FieldDev *__restrict__ fds,
     unsigned c = 0;
     for (int w = 0; w < T / 64; ++w) c += (s_wext[w] >> (16 * tid)) & 0xffffu;
     xo.tstat[4 * (size_t)bt.gt + tid] = c;
+    static_assert(kFMaxima == 0 && kFMinima == 1, "by thread");
+    if (xo.direct && c) atomicAdd(fc + tid, (unsigned long long)c);
   } else if (tid == 64) {
     float sum = 0.f;
     for (int w = 0; w < T / 64; ++w) sum += s_wsum[w];
@@ -853,6 +887,7 @@ k_tile_local(const FieldDev *__restrict__ fds,
     xo.seg[bt.gt] =
         Seg{bt.gt * (uint32_t)(2 * C::kHalo), (uint16_t)na, (uint16_t)nd};
     xo.tstat[4 * (size_t)bt.gt + 3] = na + nd;
+    if (xo.direct) atomicAdd(fc + kFExits, (unsigned long long)(na + nd));
   }
 }
 
@@ -876,18 +911,137 @@ __device__ __forceinline__ Tile tile_of_vertex(const Geo &g, uint32_t v,
   return Tile{(int)(tx * C::TX), (int)(ty * C::TY), (int)(tz * C::TZ)};
 }
 
+// Capacity of a pair table: a power of two at least twice the number of
+// distinct pairs there can be (at most 2^32, so that the mask fits 32 bits).
+__host__ __device__ inline uint64_t table_capacity(uint64_t n, uint64_t nmax,
+                                                   uint64_t nmin) {
+  uint64_t bound = nmax * nmin;
+  if (nmax != 0 && bound / nmax != nmin) bound = n;  // product overflowed
+  if (bound > n) bound = n;
+  uint64_t cap = 1024;
+  while (cap < 2 * bound && cap < (1ull << 32)) cap <<= 1;
+  return cap;
+}
+
+// First capacity tried: the bound above, or twice an expected cell count of
+// 8 per extremum (plus slack) when that is smaller, or the caller's choice.
+// Cells are pairs of manifolds that meet, far fewer than all pairs of
+// extrema: smooth, Perlin and pure-noise fields alike have 2 to 4 per
+// extremum, so the table stays at most a quarter full and short to clear; a
+// field with more makes the pair pass overflow and run again on the table of
+// the full capacity.
+__host__ __device__ inline uint64_t table_first_capacity(uint64_t n,
+                                                         uint64_t nmax,
+                                                         uint64_t nmin,
+                                                         uint64_t requested) {
+  const uint64_t full = table_capacity(n, nmax, nmin);
+  uint64_t cap = 1024;
+  const uint64_t want = requested ? (requested + 1) / 2
+                                  : 8 * (nmax + nmin) + 4096;
+  while (cap < 2 * want && cap < full) cap <<= 1;
+  return cap;
+}
+
+// Chooses the pair table capacity of every field that wants cells, on the
+// device from its extremum counts, and clears the tables, with `nb` blocks of
+// which this is number `b`: the first capacity, or (`regrow`), when the first
+// pair pass overflowed, the capacity that always suffices, with the cell
+// counters cleared for the second pass.  The host reserved each field's region
+// for the largest capacity its vertex count allows.  Every block works the
+// capacities out for itself (a launch of its own for them costs 4 us); the
+// first one records them.
+struct ClearArgs {
+  FieldDev *fds;
+  int nfields;
+  unsigned long long *fctr;
+  uint64_t requested;
+  uint32_t *tstat;
+  uint32_t nt;
+};
+
+constexpr unsigned kClearBlocks = 2048;
+
+// The fields' tables as a block sees them, kBlock fields at a time: a thread
+// per field looks it up, so a batch of 90 fields is not 90 round trips.
+struct ClearTabs {
+  uint64_t cap[kBlock];
+  unsigned long long *keys[kBlock];
+  int32_t *vals[kBlock];
+};
+
+__device__ __forceinline__ void clear_tables(const ClearArgs &c, ClearTabs &s,
+                                             uint32_t b, uint32_t nb,
+                                             bool regrow) {
+  const uint64_t stride = (uint64_t)nb * kBlock;
+  if (regrow)
+    for (uint64_t k = (uint64_t)b * kBlock + threadIdx.x; k < c.nt; k += stride)
+      c.tstat[4 * k + 2] = 0;
+  for (int i0 = 0; i0 < c.nfields; i0 += kBlock) {
+    const int i = i0 + (int)threadIdx.x;
+    if (i < c.nfields) {
+      FieldDev &fd = c.fds[i];
+      unsigned long long *fc = c.fctr + (size_t)i * kFieldCtrs;
+      const unsigned long long nmax = fc[kFMaxima], nmin = fc[kFMinima];
+      const uint64_t cap =
+          !fd.ms ? 0
+                 : (regrow ? table_capacity(fd.g.N, nmax, nmin)
+                           : table_first_capacity(fd.g.N, nmax, nmin,
+                                                  c.requested));
+      s.cap[threadIdx.x] = cap;
+      s.keys[threadIdx.x] = fd.keys;
+      s.vals[threadIdx.x] = fd.vals;
+      if (b == 0 && cap) {
+        fd.mask = (uint32_t)(cap - 1);
+        if (regrow) fc[kFCells] = 0;
+      }
+    }
+    __syncthreads();
+    const int nf = min(c.nfields - i0, kBlock);
+    for (int j = 0; j < nf; ++j) {
+      const uint64_t cap = s.cap[j];
+      unsigned long long *const keys = s.keys[j];
+      int32_t *const vals = s.vals[j];
+      // Each field's first share goes to another block (tables are small).
+      const uint64_t first = (b + 37u * (uint32_t)j) % nb;
+      for (uint64_t k = first * kBlock + threadIdx.x; k < cap; k += stride) {
+        keys[k] = kEmptyKey;
+        vals[k] = INT32_MAX;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_table_regrow(ClearArgs c, const unsigned long long *__restrict__ ctr) {
+  __shared__ ClearTabs tabs;
+  if (ctr[kCtrOverflow] & kOverflowFirst)
+    clear_tables(c, tabs, blockIdx.x, gridDim.x, true);
+}
+
 // One block per tile links the tile's exits: exit k is the halo vertex v at
 // tile-plus-halo index tlist[k]; its successor is the code that v's owner
 // tile (a face, edge or corner neighbour, found from the index) stored for
 // v -- an extremum of that tile (final) or one of that tile's exits (the
-// next node of the graph).
+// next node of the graph).  The first `cb` blocks clear the pair tables
+// instead, which nothing of this pass needs (as a launch of its own the clear
+// takes 5 us where it has next to nothing to do).
 template <class C>
 __global__ void __launch_bounds__(kBlock)
-k_exit_link(const FieldDev *__restrict__ fds,
-            const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
-            const uint16_t *__restrict__ tlist,
-            const uint32_t *__restrict__ xs, uint32_t *__restrict__ next) {
-  const BlockTile bt = block_tile(fds, tfield);
+k_exit_link(const FieldDev *fds, const uint32_t *__restrict__ tfield,
+            const Seg *__restrict__ seg, const uint16_t *__restrict__ tlist,
+            const uint32_t *__restrict__ xs, uint32_t *__restrict__ next,
+            ClearArgs clear, uint32_t cb) {
+  __shared__ ClearTabs tabs;
+  if (blockIdx.x < cb) {
+    clear_tables(clear, tabs, blockIdx.x, cb, false);
+    return;
+  }
+  BlockTile bt;
+  bt.gt = tile_of_block(blockIdx.x - cb, gridDim.x - cb);
+  bt.fi = tfield[bt.gt];
+  bt.fd = fds[bt.fi];
+  bt.tile = bt.gt - bt.fd.tile0;
   const Seg sg = seg[bt.gt];
   const uint32_t n = (uint32_t)sg.na + sg.nd;
   const uint16_t *tl = tlist + (size_t)bt.gt * (2 * C::kHalo);
@@ -965,19 +1119,25 @@ k_exit_link(const FieldDev *__restrict__ fds,
 // its own path to a final value, whatever has been resolved already.
 constexpr int kTileBuckets = 4096;
 
-// The ordering kernels run 1024-thread blocks and fold per block in LDS
-// first: tile means crowd into a few buckets, and global atomics on one
-// address serialise across the chip.
-constexpr int kOrderBlock = 1024;
-
-inline unsigned order_grid(uint32_t n) {
-  return (n + kOrderBlock - 1) / kOrderBlock;
-}
-
+// Range of the tiles' keys; the maxima, minima and exits of every tile (tile
+// counters 0, 1 and 3) are folded into their fields' here too.
 __global__ void __launch_bounds__(kOrderBlock)
-k_key_minmax(const uint32_t *__restrict__ key, uint32_t n, uint32_t *mm) {
-  __shared__ uint32_t s_lo[kOrderBlock / 64], s_hi[kOrderBlock / 64];
-  const uint32_t i = blockIdx.x * kOrderBlock + threadIdx.x;
+k_key_minmax(const uint32_t *__restrict__ key, uint32_t n, uint32_t *mm,
+             const uint32_t *__restrict__ tstat,
+             const uint32_t *__restrict__ tfield, unsigned long long *fctr) {
+  constexpr int NW = kOrderBlock / 64;
+  __shared__ uint32_t s_lo[NW], s_hi[NW];
+  const uint32_t i0 = blockIdx.x * kOrderBlock, i = i0 + threadIdx.x;
+  {
+    const bool in = i < n;
+    const uint4 c = in ? reinterpret_cast<const uint4 *>(tstat)[i]
+                       : make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t fi = in ? tfield[i] : 0u;
+    const bool uniform = !__syncthreads_or(in && fi != tfield[i0]);
+    fold_stat_block<NW>(in, c.x, fi, uniform, s_lo, fctr, kFMaxima);
+    fold_stat_block<NW>(in, c.y, fi, uniform, s_lo, fctr, kFMinima);
+    fold_stat_block<NW>(in, c.w, fi, uniform, s_lo, fctr, kFExits);
+  }
   uint32_t lo = ~0u, hi = 0;
   if (i < n) lo = hi = key[i];
   for (int o = 32; o > 0; o >>= 1) {
@@ -1433,7 +1593,8 @@ __attribute__((amdgpu_waves_per_eu(pair_waves<C>(), pair_waves<C>())))
 k_tile_pairs(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, unsigned long long *ctr,
-             uint32_t *tstat, uint16_t *tlist, uint32_t *cidx) {
+             uint32_t *tstat, uint16_t *tlist, uint32_t *cidx,
+             unsigned long long *dcells) {
   static_assert(C::TZ % 4 == 0, "four planes per index word");
   __shared__ Decode<C> s;
   __shared__ uint32_t s_fresh[C::kThreads / 64];
@@ -1544,7 +1705,8 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
     }
   }
   if (tid == 0) rec[0] = indexed ? n : 0u;
-  // New pairs this tile inserted: summed per tile, folded per field later.
+  // New pairs this tile inserted: summed per tile, folded per field later, or
+  // at once into the fields' cell counters `dcells`.
   for (int o = 32; o > 0; o >>= 1) fresh += __shfl_xor(fresh, o);
   if ((tid & 63) == 0) s_fresh[tid >> 6] = fresh;
   if (overflow) atomicOr(ctr + kCtrOverflow, kOverflowFirst);
@@ -1573,7 +1735,9 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
   if (tid == 0) {
     uint32_t c = 0;
     for (int w = 0; w < C::kThreads / 64; ++w) c += s_fresh[w];
-    ts[2] = c;
+    if (!dcells) ts[2] = c;
+    else if (c) atomicAdd(dcells + (size_t)bt.fi * kFieldCtrs,
+                          (unsigned long long)c);
   }
 }
 
@@ -1602,7 +1766,8 @@ __global__ void __launch_bounds__(C::kThreads)
 k_tile_slabs(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, unsigned long long *ctr,
-             uint32_t *tstat, uint32_t ntiles, bool again, uint16_t *tlist) {
+             uint32_t *tstat, uint32_t ntiles, bool again, uint16_t *tlist,
+             unsigned long long *dcells) {
   constexpr int T = C::kThreads, NS = C::TZ / kSlabZ, SLOTS = kSlabZ * T;
   static_assert(C::TZ % kSlabZ == 0 && (SLOTS & (SLOTS - 1)) == 0, "slabs");
   __shared__ Decode<C> s;
@@ -1693,7 +1858,11 @@ k_tile_slabs(const FieldDev *__restrict__ fds,
       for (int k = 0; k < kSlabZ; ++k)
         if (k < nz) plane_ptr(bt.fd.ms, g, t.z0 + z0 + k)[col] = sval[slot[k]];
       if (tid == 0) {
-        if (s_fresh) atomicAdd(&tstat[4 * (size_t)bt.gt + 2], s_fresh);
+        if (s_fresh && dcells)
+          atomicAdd(dcells + (size_t)bt.fi * kFieldCtrs,
+                    (unsigned long long)s_fresh);
+        else if (s_fresh)
+          atomicAdd(&tstat[4 * (size_t)bt.gt + 2], s_fresh);
         if (slab == 0) cell_record<C>(tlist, bt.gt)[0] = 0;
       }
       __syncthreads();  // the LDS tables are cleared for the next tile
@@ -1701,25 +1870,83 @@ k_tile_slabs(const FieldDev *__restrict__ fds,
   }
 }
 
+// The call's counters as the stats calls read them, in the call record's
+// pinned memory: written by a block of the last kernel (everything that counts
+// has run by then), where two small copies would take 10 us of the stream.
+// With few tiles the exit resolution's `nr` records are folded here too.
+struct HostOut {
+  const unsigned long long *ctr, *fctr, *rstat;
+  unsigned long long *hctr, *hfctr;
+  int nfields;
+  uint32_t nr;
+};
+
+__device__ __forceinline__ void st_host(unsigned long long *p,
+                                        unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <int T>
+__device__ __forceinline__ void host_out(const HostOut &h,
+                                         unsigned long long *s_mx,
+                                         unsigned long long *s_sum) {
+  const int tid = threadIdx.x;
+  unsigned long long mx = 0, sum = 0;
+  for (uint32_t i = tid; i < h.nr; i += T) {
+    const unsigned long long m = h.rstat[2 * (size_t)i];
+    mx = m > mx ? m : mx;
+    sum += h.rstat[2 * (size_t)i + 1];
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long a = __shfl_xor(mx, o);
+    mx = a > mx ? a : mx;
+    sum += __shfl_xor(sum, o);
+  }
+  if ((tid & 63) == 0) {
+    s_mx[tid >> 6] = mx;
+    s_sum[tid >> 6] = sum;
+  }
+  __syncthreads();
+  if (tid < kNumCounters) {
+    unsigned long long v = h.ctr[tid];
+    if (h.nr && tid == kCtrRounds)
+      for (int w = 0; w < T / 64; ++w) v = s_mx[w] > v ? s_mx[w] : v;
+    if (h.nr && tid == kCtrSteps)
+      for (int w = 0; w < T / 64; ++w) v += s_sum[w];
+    st_host(h.hctr + tid, v);
+  }
+  for (int i = tid; i < h.nfields * kFieldCtrs; i += T)
+    st_host(h.hfctr + i, h.fctr[i]);
+}
+
 template <class C>
 __global__ void __launch_bounds__(C::kThreads)
 k_tile_write(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, uint16_t *tlist,
-             const uint32_t *__restrict__ cidx) {
+             const uint32_t *__restrict__ cidx, HostOut ho) {
   __shared__ Decode<C> s;
   __shared__ int32_t scell[kCellIdx + 1];
+  __shared__ unsigned long long s_red[2][C::kThreads / 64];
   static_assert(kCellIdx <= (unsigned)C::kThreads, "a slot per thread");
   const int tid = threadIdx.x;
+  const uint32_t nb = gridDim.x - 1;  // the last block has no tile
+  if (blockIdx.x == nb) {
+    host_out<C::kThreads>(ho, s_red[0], s_red[1]);
+    return;
+  }
+  BlockTile bt;
+  bt.gt = tile_of_block(blockIdx.x, nb);
   // The tile's cell record needs only the tile index, so its count and
   // every slot it can hold (the record spans kHalo words) are loaded first,
   // together with the tile's descriptors; the cell ids and the bytes follow
   // in one more round trip.
-  const uint32_t *rec =
-      cell_record<C>(tlist, tile_of_block(blockIdx.x, gridDim.x));
+  const uint32_t *rec = cell_record<C>(tlist, bt.gt);
   const uint32_t r0 = rec[0];
   const uint32_t rk = rec[1 + ((unsigned)tid < kCellIdx ? tid : 0)];
-  const BlockTile bt = block_tile(fds, tfield);
+  bt.fi = tfield[bt.gt];
+  bt.fd = fds[bt.fi];
+  bt.tile = bt.gt - bt.fd.tile0;
   const Geo &g = bt.fd.g;
   int32_t *const ms = bt.fd.ms;
   const Tile t = tile_at<C>(g, bt.tile);
@@ -1794,112 +2021,43 @@ __global__ void k_fill_u64(unsigned long long *p, uint32_t n,
   if (i < n) p[i] = value;
 }
 
-// Capacity of a pair table: a power of two at least twice the number of
-// distinct pairs there can be (at most 2^32, so that the mask fits 32 bits).
-__host__ __device__ inline uint64_t table_capacity(uint64_t n, uint64_t nmax,
-                                                   uint64_t nmin) {
-  uint64_t bound = nmax * nmin;
-  if (nmax != 0 && bound / nmax != nmin) bound = n;  // product overflowed
-  if (bound > n) bound = n;
-  uint64_t cap = 1024;
-  while (cap < 2 * bound && cap < (1ull << 32)) cap <<= 1;
-  return cap;
-}
-
-// First capacity tried: the bound above, or twice an expected cell count of
-// 8 per extremum (plus slack) when that is smaller, or the caller's choice.
-// Cells are pairs of manifolds that meet, far fewer than all pairs of
-// extrema: smooth, Perlin and pure-noise fields alike have 2 to 4 per
-// extremum, so the table stays at most a quarter full and short to clear; a
-// field with more makes the pair pass overflow and run again on the table of
-// the full capacity.
-__host__ __device__ inline uint64_t table_first_capacity(uint64_t n,
-                                                         uint64_t nmax,
-                                                         uint64_t nmin,
-                                                         uint64_t requested) {
-  const uint64_t full = table_capacity(n, nmax, nmin);
-  uint64_t cap = 1024;
-  const uint64_t want = requested ? (requested + 1) / 2
-                                  : 8 * (nmax + nmin) + 4096;
-  while (cap < 2 * want && cap < full) cap <<= 1;
-  return cap;
-}
-
-// The tile -> field map, from the fields' first tiles (increasing).
-__global__ void __launch_bounds__(kBlock)
-k_fill_tfield(const FieldDev *__restrict__ fds, int nfields, uint32_t *tfield,
-              uint32_t nt) {
-  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= nt) return;
-  int lo = 0, hi = nfields - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (fds[mid].tile0 <= i) lo = mid;
-    else hi = mid - 1;
-  }
-  tfield[i] = (uint32_t)lo;
-}
+// A batch's descriptors as a kernel argument, where they are few.
+template <int B>
+struct FieldArgs {
+  FieldDev f[B];
+};
+constexpr int kArgFields = 24;  // 2.7 KB of the 4 KB of arguments
 
 // Everything a call clears or fills before its first pass, in one launch:
-// the counter block, the tile -> field map, the per-field counters, the
-// tile-order histogram with its min/max pair (min starts at ~0), and the
+// the counter block, the descriptors (from the arguments; with more of them a
+// copy, which takes 10 us of the stream, has put them there), the tile ->
+// field map, the per-field counters, the tile-order histogram with its min/max
+// pair (min starts at ~0; NULL when the tiles are not ordered), and the
 // per-tile counters.
+template <int B>
 __global__ void __launch_bounds__(kBlock)
-k_call_setup(const FieldDev *__restrict__ fds, int nfields, uint32_t nt,
-             unsigned long long *ctr, uint32_t *tfield,
+k_call_setup(FieldArgs<B ? B : 1> args, FieldDev *fds, int nfields,
+             uint32_t nt, unsigned long long *ctr, uint32_t *tfield,
              unsigned long long *fctr, uint32_t *hist, uint32_t *tstat) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  static_assert(sizeof(FieldDev) % 4 == 0, "copied by words");
+  const FieldDev *const src = B ? args.f : fds;
+  if (B && i < (uint32_t)nfields * (uint32_t)(sizeof(FieldDev) / 4))
+    reinterpret_cast<uint32_t *>(fds)[i] =
+        reinterpret_cast<const uint32_t *>(src)[i];
   if (i < (uint32_t)kNumCounters) ctr[i] = 0ull;
   if (i < (uint32_t)nfields * kFieldCtrs) fctr[i] = 0ull;
-  if (i < (uint32_t)kTileBuckets + 2)
+  if (hist && i < (uint32_t)kTileBuckets + 2)
     hist[i] = i == (uint32_t)kTileBuckets ? ~0u : 0u;
   if (i < nt) {
     int lo = 0, hi = nfields - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (fds[mid].tile0 <= i) lo = mid;
+      if (src[mid].tile0 <= i) lo = mid;
       else hi = mid - 1;
     }
     tfield[i] = (uint32_t)lo;
     reinterpret_cast<uint4 *>(tstat)[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
-}
-
-// Chooses the pair table capacity of every field that wants cells, on the
-// device from its extremum counts, and clears the tables over a fixed grid:
-// the first capacity, or (`regrow`), when the first pair pass overflowed, the
-// capacity that always suffices, with the tiles' cell counters cleared for the
-// second pass; without an overflow there is nothing to do then.  The host
-// reserved each field's region for the largest capacity its vertex count
-// allows.  Every block works the capacities out for itself (a launch of its
-// own for them costs 4 us); the first one records them.
-constexpr unsigned kClearBlocks = 2048;
-
-__global__ void __launch_bounds__(kBlock)
-k_table_clear_all(FieldDev *fds, int nfields,
-                  const unsigned long long *__restrict__ fctr,
-                  const unsigned long long *__restrict__ ctr,
-                  uint64_t requested, bool regrow, uint32_t *tstat,
-                  uint32_t nt) {
-  if (regrow && !(ctr[kCtrOverflow] & kOverflowFirst)) return;
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  const uint64_t k0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (regrow)
-    for (uint64_t k = k0; k < nt; k += stride) tstat[4 * k + 2] = 0;
-  for (int i = 0; i < nfields; ++i) {
-    if (!fds[i].ms) continue;
-    unsigned long long *const keys = fds[i].keys;
-    int32_t *const vals = fds[i].vals;
-    const uint64_t n = fds[i].g.N;
-    const unsigned long long *fc = fctr + (size_t)i * kFieldCtrs;
-    const uint64_t cap =
-        regrow ? table_capacity(n, fc[kFMaxima], fc[kFMinima])
-               : table_first_capacity(n, fc[kFMaxima], fc[kFMinima], requested);
-    if (k0 == 0) fds[i].mask = (uint32_t)(cap - 1);
-    for (uint64_t k = k0; k < cap; k += stride) {
-      keys[k] = kEmptyKey;
-      vals[k] = INT32_MAX;
-    }
   }
 }
 
@@ -1935,10 +2093,13 @@ int take_call(msc_ctx *ctx, int nfields, int *index) {
     R.hctr = nullptr;
     return MSC_ENOMEM;
   }
+  if (!R.dhctr)
+    MSC_HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&R.dhctr),
+                                        R.hctr, 0));
   const size_t want = (size_t)nfields * kFieldCtrs;
   if (want > R.hfctr_cap) {
     if (R.hfctr) (void)hipHostFree(R.hfctr);
-    R.hfctr = nullptr;
+    R.hfctr = R.dhfctr = nullptr;
     R.hfctr_cap = 0;
     const size_t cap = want * 2 + 64;
     if (host_malloc(reinterpret_cast<void **>(&R.hfctr), cap * 8) !=
@@ -1948,6 +2109,9 @@ int take_call(msc_ctx *ctx, int nfields, int *index) {
     }
     R.hfctr_cap = cap;
   }
+  if (!R.dhfctr)
+    MSC_HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&R.dhfctr),
+                                        R.hfctr, 0));
   ctx->next_call = (k + 1) % kCallRing;
   *index = k;
   return MSC_OK;
@@ -2163,85 +2327,97 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
                                                (C::TZ / 4))
                           : nullptr;
 
-  // The descriptors go up through a pinned slot; the tile -> field map is
-  // built on the device.
+  CallRec &R = ctx->calls[rec];
+  const bool direct = nt <= kDirectTiles;
   {
-    void *st = nullptr;
-    int slot = 0;
-    const size_t fbytes = nfields * sizeof(FieldDev);
-    MSC_TRY(pinned_slot(ctx, fbytes, &st, &slot));
-    std::memcpy(st, fd.data(), fbytes);
-    MSC_HIP_TRY(hipMemcpyAsync(fds, st, fbytes, hipMemcpyHostToDevice, s));
-    MSC_TRY(slot_copied(ctx, slot, s));
-  }
-  {
-    const uint64_t span = std::max<uint64_t>(
-        std::max<uint64_t>(nt, (uint64_t)nfields * kFieldCtrs),
-        std::max<uint64_t>(kTileBuckets + 2, kNumCounters));
-    k_call_setup<<<grid_for(span), kBlock, 0, s>>>(fds, nfields, nt, ctr,
-                                                   tfield, fctr, hist, tstat);
+    auto setup = [&](auto b) {
+      constexpr int B = decltype(b)::value;
+      FieldArgs<B ? B : 1> args;
+      if (B) std::memcpy(args.f, fd.data(), nfields * sizeof(FieldDev));
+      const uint64_t span = std::max<uint64_t>(
+          std::max<uint64_t>(nt, B ? nfields * (sizeof(FieldDev) / 4)
+                                   : (uint64_t)nfields * kFieldCtrs),
+          direct ? kNumCounters : kTileBuckets + 2);
+      k_call_setup<B><<<grid_for(span), kBlock, 0, s>>>(
+          args, fds, nfields, nt, ctr, tfield, fctr, direct ? nullptr : hist,
+          tstat);
+    };
+    if (nfields == 1) {
+      setup(std::integral_constant<int, 1>());
+    } else if (nfields <= kArgFields) {
+      setup(std::integral_constant<int, kArgFields>());
+    } else {
+      // The descriptors go up through a pinned slot.
+      void *st = nullptr;
+      int slot = 0;
+      const size_t fbytes = nfields * sizeof(FieldDev);
+      MSC_TRY(pinned_slot(ctx, fbytes, &st, &slot));
+      std::memcpy(st, fd.data(), fbytes);
+      MSC_HIP_TRY(hipMemcpyAsync(fds, st, fbytes, hipMemcpyHostToDevice, s));
+      MSC_TRY(slot_copied(ctx, slot, s));
+      setup(std::integral_constant<int, 0>());
+    }
   }
   MSC_HIP_TRY(hipGetLastError());
-  ExitOut xo{seg, tkey, tstat, tlist, xs};
+  ExitOut xo{seg, tkey, tstat, tlist, xs, direct};
   MSC_PHASE(ctx, s, "tile_local", 12.0 * total_n,
             (k_tile_local<C><<<nt, C::kThreads, 0, s>>>(fds, tfield, xo, ctr,
                                                         fctr)));
-  k_tile_stats3<<<grid_for(nt), kBlock, 0, s>>>(tstat, nt, tfield, fctr);
+  // The link pass clears the pair tables, whose size needs the extremum
+  // counts, so the counters and the order come first.
+  if (!direct)
+    MSC_PHASE(ctx, s, "tile_order", 12.0 * nt,
+              (k_key_minmax<<<order_grid(nt), kOrderBlock, 0, s>>>(
+                   tkey, nt, mm, tstat, tfield, fctr),
+               k_key_hist<<<order_grid(nt), kOrderBlock, 0, s>>>(tkey, nt, mm,
+                                                                hist),
+               k_key_scan<<<1, 1024, 0, s>>>(hist),
+               k_key_scatter<<<order_grid(nt), kOrderBlock, 0, s>>>(
+                   tkey, nt, mm, hist, seg, oseg)));
   // Exit slots are fixed per tile (2 * kHalo from the tile's own base), so
   // no count has to come back to the host before the graph is built.
+  const ClearArgs clear{fds, nfields, fctr, ctx->table_first, tstat, nt};
+  const unsigned cb = any_ms ? (unsigned)std::min<uint64_t>(
+                                   kClearBlocks, (tab_slots + kBlock - 1) / kBlock)
+                             : 0u;
   MSC_PHASE(ctx, s, "exit_link", 10.0 * nt * (double)C::kHalo * 0.5,
-            (k_exit_link<C><<<nt, kBlock, 0, s>>>(fds, tfield, seg, tlist,
-                                                  xs, next)));
-  MSC_PHASE(ctx, s, "tile_order", 12.0 * nt,
-            (k_key_minmax<<<order_grid(nt), kOrderBlock, 0, s>>>(tkey, nt,
-                                                                 mm),
-             k_key_hist<<<order_grid(nt), kOrderBlock, 0, s>>>(tkey, nt, mm,
-                                                              hist),
-             k_key_scan<<<1, 1024, 0, s>>>(hist),
-             k_key_scatter<<<order_grid(nt), kOrderBlock, 0, s>>>(
-                 tkey, nt, mm, hist, seg, oseg)));
+            (k_exit_link<C><<<nt + cb, kBlock, 0, s>>>(fds, tfield, seg, tlist,
+                                                       xs, next, clear, cb)));
   MSC_PHASE(ctx, s, "exit_resolve", 12.0 * nt * (double)C::kHalo * 0.5,
             (k_exit_resolve<<<2 * nt, kResolveThreads, 0, s>>>(
-                oseg, nt, nslots, next, ctr, rstat)));
-  k_steps_reduce<<<kStepsBlocks, 1024, 0, s>>>(rstat, 2 * nt, ctr);
+                direct ? seg : oseg, nt, nslots, next, ctr, rstat)));
+  if (!direct)
+    k_steps_reduce<<<kStepsBlocks, 1024, 0, s>>>(rstat, 2 * nt, ctr);
 
   if (any_ms) {
     // Pair tables sized on the device; a pass that overflows its first
     // table runs once more on the capacity that always suffices (the second
     // pass and its clear return at once when nothing overflowed).
-    const unsigned cb = (unsigned)std::min<uint64_t>(
-        kClearBlocks, (tab_slots + kBlock - 1) / kBlock);
-    MSC_PHASE(ctx, s, "table_clear", 12.0 * total_n,
-              (k_table_clear_all<<<cb, kBlock, 0, s>>>(
-                  fds, nfields, fctr, ctr, ctx->table_first, false, tstat,
-                  nt)));
+    unsigned long long *const dcells = direct ? fctr + kFCells : nullptr;
     MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
               (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
-                  fds, tfield, seg, next, ctr, tstat, tlist, cidx)));
+                  fds, tfield, seg, next, ctr, tstat, tlist, cidx, dcells)));
     const unsigned sb =
         std::min<uint64_t>((uint64_t)nt * (C::TZ / kSlabZ), kSlabBlocks);
     MSC_PHASE(ctx, s, "tile_slabs", 0.0,
               (k_tile_slabs<C><<<sb, C::kThreads, 0, s>>>(
-                  fds, tfield, seg, next, ctr, tstat, nt, false, tlist)));
-    k_table_clear_all<<<cb, kBlock, 0, s>>>(fds, nfields, fctr, ctr,
-                                            ctx->table_first, true, tstat, nt);
+                  fds, tfield, seg, next, ctr, tstat, nt, false, tlist,
+                  dcells)));
+    k_table_regrow<<<cb, kBlock, 0, s>>>(clear, ctr);
     k_tile_slabs<C><<<sb, C::kThreads, 0, s>>>(fds, tfield, seg, next, ctr,
-                                               tstat, nt, true, tlist);
+                                               tstat, nt, true, tlist, dcells);
     MSC_HIP_TRY(hipGetLastError());
-    k_tile_stat_reduce<<<grid_for(nt), kBlock, 0, s>>>(tstat, 2, nt, tfield,
-                                                       fctr, kFCells);
+    if (!direct)
+      k_tile_cells<<<order_grid(nt), kOrderBlock, 0, s>>>(tstat, nt, tfield,
+                                                          fctr);
   }
+  const HostOut ho{ctr, fctr, rstat, R.dhctr, R.dhfctr, nfields,
+                   direct ? 2 * nt : 0u};
   MSC_PHASE(ctx, s, "tile_write", (any_ms ? 5.0 : 12.0) * total_n,
-            (k_tile_write<C><<<nt, C::kThreads, 0, s>>>(fds, tfield, seg,
-                                                        next, tlist, cidx)));
-  // Counters back to the record's pinned memory, for the stats calls.
-  CallRec &R = ctx->calls[rec];
-  MSC_HIP_TRY(hipMemcpyAsync(R.hfctr, fctr, (size_t)nfields * kFieldCtrs * 8,
-                             hipMemcpyDeviceToHost, s));
-  MSC_HIP_TRY(hipMemcpyAsync(R.hctr, ctr, kNumCounters * 8,
-                             hipMemcpyDeviceToHost, s));
+            (k_tile_write<C><<<nt + 1, C::kThreads, 0, s>>>(
+                fds, tfield, seg, next, tlist, cidx, ho)));
   MSC_HIP_TRY(hipEventRecord(R.done, s));
-  MSC_TRY(end_call(ctx, s));
+  MSC_TRY(end_call(ctx, s, R.done));
   R.pending = true;
   R.nfields = nfields;
   R.n.resize(nfields);

@@ -120,3 +120,47 @@ def test_autotune_keeps_results(msc):
             np.testing.assert_array_equal(m.cpu().numpy(), want[2])
     finally:
         msc.set_tile(*msc.tile_shapes()[0])
+
+
+def oracle_counts(want):
+    asc, desc, ms = want
+    return [np.unique(x).size for x in (asc, desc, ms)]
+
+
+@pytest.mark.parametrize("count", [1, 2, 23, 24, 25])
+def test_descriptors_and_counts(msc, count):
+    """Batches around the number of descriptors that travel as kernel
+    arguments: every label and every field's counts."""
+    rng = np.random.default_rng(count)
+    fs = [synth.random_field(rng.integers(1, 40, size=3), seed=100 + i,
+                             levels=5 if i % 3 else None)
+          for i in range(count)]
+    outs = msc.segment_batched([torch.from_numpy(f).cuda() for f in fs])
+    for i, (f, out) in enumerate(zip(fs, outs)):
+        want = O.segment(f)
+        for g, w in zip(out, want):
+            np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=f"{i}")
+        st = msc.last_field_stats(i)
+        assert [st["n_maxima"], st["n_minima"], st["n_cells"]] == \
+            oracle_counts(want), i
+        assert st["n_vertices"] == f.size
+
+
+@pytest.mark.parametrize("shapes", [[(2048, 1024, 1)], [(2048, 1025, 1)],
+                                    [(2048, 1000, 1), (1500, 90, 20),
+                                     (33, 17, 18)]])
+def test_counts_folded_at_once_and_later(msc, shapes):
+    """Calls of 4,096 tiles, just above, and well above over several fields:
+    labels, counts and the exit statistics' presence."""
+    fs = [synth.random_field(d, seed=7 + i) for i, d in enumerate(shapes)]
+    outs = msc.segment_batched([torch.from_numpy(f).cuda() for f in fs])
+    for i, (f, out) in enumerate(zip(fs, outs)):
+        want = O.segment(f)
+        for g, w in zip(out, want):
+            np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=f"{i}")
+        st = msc.last_field_stats(i)
+        assert [st["n_maxima"], st["n_minima"], st["n_cells"]] == \
+            oracle_counts(want), i
+        assert st["n_exits"] > 0
+    st = msc.last_stats()
+    assert st["jump_rounds"] >= 1 and st["exit_steps"] >= st["jump_rounds"]
