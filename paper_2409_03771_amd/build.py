@@ -19,6 +19,8 @@ FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", f"--offload-arch={ARCH}",
     # Keep the compiler from emitting packed FP32 arithmetic.
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # The link tables (2^14 sets) are made by the compiler.
+    "-fconstexpr-steps=100000000",
     "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"),
 ]

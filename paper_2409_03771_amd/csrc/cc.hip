@@ -22,6 +22,7 @@
 //   cc_final   label = root of the vertex's tile-local root.
 // CSR graphs have no locality to exploit: init to the smallest masked
 // neighbour, one union per listed edge, then a final find per vertex.
+#include <algorithm>
 #include <climits>
 #include <mutex>
 
@@ -1555,6 +1556,22 @@ constexpr NbVec kNb[14] = {
     {0, -1, 0},   {-1, 0, 0},  {1, 0, 0},   {0, 1, 0},  {1, 1, 0},
     {0, 0, 1},    {1, 0, 1},   {0, 1, 1},   {1, 1, 1}};
 
+// A coordinate of every neighbour, two bits each (the step plus one).
+constexpr uint32_t pack_steps(int axis) {
+  uint32_t p = 0;
+  for (int i = 0; i < 14; ++i) {
+    const int d = axis == 0 ? kNb[i].dx : (axis == 1 ? kNb[i].dy : kNb[i].dz);
+    p |= (uint32_t)(d + 1) << (2 * i);
+  }
+  return p;
+}
+constexpr uint32_t kNbX = pack_steps(0), kNbY = pack_steps(1),
+                   kNbZ = pack_steps(2);
+
+__device__ __forceinline__ int64_t nb_step(uint32_t steps, int i) {
+  return (int64_t)((steps >> (2 * i)) & 3u) - 1;
+}
+
 constexpr bool edge_vector(int a, int b, int c) {
   const bool nonneg = a >= 0 && b >= 0 && c >= 0 && a <= 1 && b <= 1 && c <= 1;
   const bool nonpos = a <= 0 && b <= 0 && c <= 0 && a >= -1 && b >= -1 &&
@@ -1573,41 +1590,38 @@ constexpr uint32_t link_adj(int i) {
 
 // Components of the link restricted to a set of neighbours depend on the set
 // alone (the adjacency is fixed and absent neighbours are simply not in the
-// set), so two tables over all 2^14 sets replace the per-vertex growth: the
-// number of components, and the component that holds the set's lowest
-// neighbour.  Removing that component leaves a set whose components are the
-// remaining ones, so repeated lookups enumerate them.
+// set), so two tables over all 2^14 sets, made when this file is compiled,
+// replace the per-vertex growth: the number of components, and the component
+// that holds the set's lowest neighbour.  Removing that component leaves a set
+// whose components are the remaining ones, so repeated lookups enumerate them.
 constexpr int kLinkSets = 1 << 14;
 
-__device__ __forceinline__ uint32_t grow_component(uint32_t seed,
-                                                   uint32_t set) {
-  uint32_t comp = seed, prev;
-  do {
-    prev = comp;
-    uint32_t g = comp;
-#pragma unroll
-    for (int i = 0; i < 14; ++i)
-      if ((prev >> i) & 1u) g |= link_adj(i);
-    comp = g & set;
-  } while (comp != prev);
-  return comp;
+struct LinkTables {
+  uint8_t ncomp[kLinkSets];
+  uint16_t first[kLinkSets];
+};
+
+constexpr LinkTables make_link_tables() {
+  LinkTables t{};
+  uint32_t adj[14] = {};
+  for (int i = 0; i < 14; ++i) adj[i] = link_adj(i);
+  for (uint32_t set = 1; set < (uint32_t)kLinkSets; ++set) {
+    // Grown from the lowest neighbour, one newly reached member at a time.
+    uint32_t comp = set & (0u - set), todo = comp;
+    while (todo) {
+      const int i = __builtin_ctz(todo);
+      todo &= todo - 1;
+      const uint32_t fresh = adj[i] & set & ~comp;
+      comp |= fresh;
+      todo |= fresh;
+    }
+    t.first[set] = (uint16_t)comp;
+    t.ncomp[set] = (uint8_t)(1 + t.ncomp[set & ~comp]);  // a smaller set
+  }
+  return t;
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_link_tables(uint8_t *__restrict__ ncomp, uint16_t *__restrict__ first) {
-  const uint32_t set = blockIdx.x * kBlock + threadIdx.x;
-  if (set >= (uint32_t)kLinkSets) return;
-  uint32_t rem = set, head = 0;
-  int count = 0;
-  while (rem) {
-    const uint32_t comp = grow_component(rem & (0u - rem), rem);
-    if (!count) head = comp;
-    rem &= ~comp;
-    ++count;
-  }
-  ncomp[set] = (uint8_t)count;
-  first[set] = (uint16_t)head;
-}
+__device__ constexpr LinkTables kLink = make_link_tables();
 
 struct LinkSets {
   float fn[14];          // neighbour values (meaningless where absent)
@@ -1669,12 +1683,12 @@ __device__ __forceinline__ LinkSets link_sets(const float *__restrict__ f,
 // `high`), as a neighbour mask.  Neighbour order is id order, so a tie in
 // value goes to the larger index for the highest and the smaller for the
 // lowest.
-__device__ __forceinline__ uint32_t component_extremes(
-    uint32_t set, const float *fn, bool high,
-    const uint16_t *__restrict__ first) {
+__device__ __forceinline__ uint32_t component_extremes(uint32_t set,
+                                                       const float *fn,
+                                                       bool high) {
   uint32_t rem = set, ex = 0;
   while (rem) {
-    const uint32_t comp = first[rem];
+    const uint32_t comp = kLink.first[rem];
     int best = -1;
     float fb = 0.f;
 #pragma unroll
@@ -1692,17 +1706,137 @@ __device__ __forceinline__ uint32_t component_extremes(
   return ex;
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_critical(const float *__restrict__ f, int64_t X, int64_t Y, int64_t Z,
-           const uint8_t *__restrict__ ncomp, uint8_t *__restrict__ code,
-           unsigned long long *ctr) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// The link sets of every vertex, for passes that take the whole grid: a thread
+// walks up z from a position p = x + X*y of the plane, so that seven loads per
+// vertex (the plane above; the others are in registers) do instead of fifteen,
+// the position's neighbours are located once per walk, and a comparison goes
+// straight from the lane mask it leaves into the set's next bit.  Consecutive
+// threads take consecutive positions, whatever the rows' length: a wave's 64
+// vertices of a plane are 64 consecutive ids (a run).  What bounds these passes
+// is vector and LDS issue, about 50 vector operations a vertex (189 with
+// fifteen loads and a vertex's own coordinates).  Critical points of 512^3 take
+// 0.28 ms instead of 0.60 (2.4 TB/s of the 5 bytes a vertex), 0.35 without the
+// load ahead.
+constexpr int kWalkThreads = 512;
+
+struct Walk {
+  const float *f;
+  uint32_t X, Y, Z, XY, runs;  // runs of 64 positions per plane
+  uint32_t pb, zc;             // blocks per plane, planes per walk
+};
+
+// idx * 2 + (the lane's bit of m).
+__device__ __forceinline__ uint32_t push_bit(uint32_t idx,
+                                             unsigned long long m) {
+  asm("v_addc_co_u32 %0, vcc, %0, %0, %1" : "+v"(idx) : "s"(m) : "vcc");
+  return idx;
+}
+
+__device__ __forceinline__ unsigned long long lanes(bool b) {
+  return __builtin_amdgcn_ballot_w64(b);
+}
+
+// Calls use(z, p, inside, lower, upper) for every plane of the block's chunk,
+// with all lanes; returns whether a value of the lane's was NaN.
+template <class Use>
+__device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
+  const uint32_t blk = cc_tile_of_block(blockIdx.x, gridDim.x);
+  const uint32_t chunk = blk / w.pb;
+  const uint32_t p0 = (blk - chunk * w.pb) * kWalkThreads + threadIdx.x;
+  const bool inside = p0 < w.XY;
+  const uint32_t p = inside ? p0 : w.XY - 1;
+  const uint32_t y = p / w.X, x = p - y * w.X;
+  const bool xl = x > 0, yl = y > 0, xh = x + 1 < w.X, yh = y + 1 < w.Y;
+  // A neighbour outside the grid is read as the position itself and is not
+  // in `here`, the neighbours that exist in the planes below, at and above.
+  const uint32_t low = (xl && yl) | (uint32_t)yl << 1 | (uint32_t)xl << 2,
+                 high = (uint32_t)xh | (uint32_t)yh << 1 |
+                        (uint32_t)(xh && yh) << 2;
+  const uint32_t here = low | 8u | low << 4 | high << 7 | 1u << 10 | high << 11;
+  const uint32_t oxl = p - (xl ? 1u : 0u), oyl = p - (yl ? w.X : 0u),
+                 oxyl = p - (xl && yl ? w.X + 1 : 0u);
+  const uint32_t oxh = p + (xh ? 1u : 0u), oyh = p + (yh ? w.X : 0u),
+                 oxyh = p + (xh && yh ? w.X + 1 : 0u);
+  struct PlaneL {
+    float xyl, yl, xl, c;
+  };
+  struct PlaneH {
+    float xh, yh, xyh;
+  };
+  typedef __attribute__((address_space(1))) const float GF;
+  auto plane = [&](uint32_t z) {
+    return (GF *)w.f + (size_t)w.XY * z;
+  };
+  auto load_l = [&](uint32_t z) {
+    GF *q = plane(z);
+    return PlaneL{q[oxyl], q[oyl], q[oxl], q[p]};
+  };
+  auto load_h = [&](uint32_t z) {
+    GF *q = plane(z);
+    return PlaneH{q[oxh], q[oyh], q[oxyh]};
+  };
+  const uint32_t z0 = chunk * w.zc;
+  const uint32_t z1 = z0 + w.zc < w.Z ? z0 + w.zc : w.Z;
+  // The plane above is loaded one step ahead of its use.
+  auto in_z = [&](uint32_t z) { return z < w.Z ? z : w.Z - 1; };
+  PlaneL below = load_l(z0 > 0 ? z0 - 1 : 0), cur = load_l(z0);
+  PlaneH curh = load_h(z0);
+  PlaneL up = load_l(in_z(z0 + 1));
+  PlaneH uph = load_h(in_z(z0 + 1));
   bool nan = false;
-  if (v < X * Y * Z) {
-    const LinkSets ls = link_sets(f, X, Y, Z, v);
-    code[v] = (uint8_t)(ncomp[ls.lower] | (ncomp[ls.upper] << 4));
-    nan = ls.nan;
+  for (uint32_t z = z0; z < z1; ++z) {
+    const PlaneL next = load_l(in_z(z + 2));
+    const PlaneH nexth = load_h(in_z(z + 2));
+    const float v = cur.c;
+    nan |= v != v;
+    // Neighbours in decreasing id; the ones with smaller ids than v are below
+    // it when equal.
+    uint32_t s = 0;
+    s = push_bit(s, lanes(uph.xyh < v));
+    s = push_bit(s, lanes(uph.yh < v));
+    s = push_bit(s, lanes(uph.xh < v));
+    s = push_bit(s, lanes(up.c < v));
+    s = push_bit(s, lanes(curh.xyh < v));
+    s = push_bit(s, lanes(curh.yh < v));
+    s = push_bit(s, lanes(curh.xh < v));
+    s = push_bit(s, lanes(cur.xl <= v));
+    s = push_bit(s, lanes(cur.yl <= v));
+    s = push_bit(s, lanes(cur.xyl <= v));
+    s = push_bit(s, lanes(below.c <= v));
+    s = push_bit(s, lanes(below.xl <= v));
+    s = push_bit(s, lanes(below.yl <= v));
+    s = push_bit(s, lanes(below.xyl <= v));
+    const uint32_t planes = (z > 0 ? 0xfu : 0u) | 0x3f0u |
+                            (z + 1 < w.Z ? 0x3c00u : 0u);  // uniform
+    const uint32_t present = here & planes;
+    use(z, p0, inside, s & present, present & ~s);
+    below = cur;
+    cur = up;
+    curh = uph;
+    up = next;
+    uph = nexth;
   }
+  return inside && nan;
+}
+
+// The count table in LDS, where both lookups of a vertex cost one read.
+__device__ __forceinline__ void stage_ncomp(uint8_t *t) {
+  const uint4 *src = reinterpret_cast<const uint4 *>(kLink.ncomp);
+  for (int i = threadIdx.x; i < kLinkSets / 16; i += kWalkThreads)
+    reinterpret_cast<uint4 *>(t)[i] = src[i];
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kWalkThreads)
+k_critical(Walk w, uint8_t *__restrict__ code, unsigned long long *ctr) {
+  __shared__ __align__(16) uint8_t nc[kLinkSets];
+  stage_ncomp(nc);
+  typedef __attribute__((address_space(1))) uint8_t GB;
+  const bool nan = walk_links(w, [&](uint32_t z, uint32_t p, bool inside,
+                                     uint32_t lower, uint32_t upper) {
+    const uint32_t c = nc[lower] | (uint32_t)nc[upper] << 4;
+    if (inside) ((GB *)code + (size_t)w.XY * z)[p] = (uint8_t)c;
+  });
   flag_any(nan, ctr + kCtrNaN);
 }
 
@@ -1741,17 +1875,135 @@ __device__ __forceinline__ uint32_t block_scan16(uint32_t x, uint32_t *tmp,
   return before + pre;
 }
 
+// The edges of vertex v from position `at` on: ascending ones first, then
+// descending; within a side, components by increasing id of their extreme
+// vertex (= neighbour order).
+__device__ __forceinline__ void egraph_emit(const LinkSets &ls, int64_t v,
+                                            int64_t X, int64_t XY, uint32_t lc,
+                                            uint32_t uc,
+                                            const int32_t *__restrict__ asc,
+                                            const int32_t *__restrict__ desc,
+                                            int32_t *__restrict__ out,
+                                            int64_t at) {
+  // Both sides' extreme neighbours in output order, one per step: the lanes
+  // of a wave then take as many steps as the vertex with most edges has, where
+  // a step per neighbour would wait for 28 gathers in turn.
+  const uint32_t hm = component_extremes(uc >= 2 ? ls.upper : 0u, ls.fn, true),
+                 lm = component_extremes(lc >= 2 ? ls.lower : 0u, ls.fn, false);
+  for (uint32_t m = hm | lm << 14; m; m &= m - 1) {
+    const int k = __ffs((int)m) - 1;
+    const bool high = k < 14;
+    const int i = high ? k : k - 14;
+    const int64_t u = v + nb_step(kNbX, i) + X * nb_step(kNbY, i) +
+                      XY * nb_step(kNbZ, i);
+    const int32_t e = (high ? asc : desc)[u];
+    out[3 * at] = (int32_t)v;
+    out[3 * at + 1] = e;
+    out[3 * at + 2] = high ? 1 : -1;
+    ++at;
+  }
+}
+
+// Every run's vertices with edges as a lane mask, and the number of the run's
+// edges; the write pass then looks at those vertices alone.
+__global__ void __launch_bounds__(kWalkThreads)
+k_egraph_mark(Walk w, unsigned long long *__restrict__ marks,
+              uint32_t *__restrict__ counts, unsigned long long *ctr) {
+  __shared__ __align__(16) uint8_t nc[kLinkSets];
+  stage_ncomp(nc);
+  const bool nan = walk_links(w, [&](uint32_t z, uint32_t p, bool inside,
+                                     uint32_t lower, uint32_t upper) {
+    const uint32_t c = inside ? edge_count(nc[lower], nc[upper]) : 0u;
+    const unsigned long long m = lanes(c != 0u);
+    uint32_t sum = 0;
+    if (m) {  // a count has four bits: a vertex has at most 14 edges
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        sum += (uint32_t)__popcll(lanes((c >> k) & 1u)) << k;
+    }
+    if ((threadIdx.x & 63) == 0 && p < w.XY) {
+      const size_t r = (size_t)w.runs * z + p / 64;
+      marks[r] = m;
+      counts[r] = sum;
+    }
+  });
+  flag_any(nan, ctr + kCtrNaN);
+}
+
+// A wave takes K consecutive runs (at most 64), lists their marked vertices in
+// LDS, and works through the list 64 at a time, so that its lanes are full
+// however the marks lie.  The edges of its runs are one contiguous stretch of
+// the output, in the list's order.  K is what holds about 32 edges: with more
+// the long lists of noisy regions are left to few waves, with fewer the lanes
+// are idle.  At 512^3 Perlin noise (0.9 % of the vertices marked) K = 64 takes
+// 0.12 ms and K = 8 0.44, at 512^3 Gaussian sums (5 %, in clusters) 0.68 and
+// 0.48; a pass over all vertices, with a step per neighbour to write the
+// edges, took 0.76 and 0.82.
 __global__ void __launch_bounds__(kBlock)
-k_egraph_count(const float *__restrict__ f, int64_t X, int64_t Y, int64_t Z,
-               const uint8_t *__restrict__ ncomp, uint32_t *bcount,
-               unsigned long long *ctr) {
+k_egraph_write(Walk w, uint64_t nruns, int K,
+               const unsigned long long *__restrict__ marks,
+               const int64_t *__restrict__ off,
+               const int32_t *__restrict__ asc,
+               const int32_t *__restrict__ desc, int32_t *__restrict__ out) {
+  __shared__ uint16_t list[kBlock / 64][64 * 64];  // run << 6 | position
+  const int lane = threadIdx.x & 63;
+  uint16_t *const mine = list[threadIdx.x >> 6];
+  const uint64_t r0 =
+      ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / 64 * (uint32_t)K;
+  const uint64_t r = r0 + lane;
+  const unsigned long long m = lane < K && r < nruns ? marks[r] : 0ull;
+  const uint32_t n = (uint32_t)__popcll(m);
+  uint32_t inc = n;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  const uint32_t total = __shfl(inc, 63);
+  uint32_t at = inc - n;
+  for (unsigned long long t = m; t; t &= t - 1)
+    mine[at++] = (uint16_t)(lane << 6 | (__ffsll((long long)t) - 1));
+  __syncthreads();
+  if (!total) return;  // uniform over the wave
+  const uint64_t z0 = r0 / w.runs;
+  const uint32_t run0 = (uint32_t)(r0 - z0 * w.runs);
+  int64_t base = off[r0];
+  for (uint32_t j = 0; j < total; j += 64) {
+    const bool on = j + lane < total;
+    const uint32_t it = mine[on ? j + lane : j];
+    const uint32_t rr = run0 + (it >> 6), dz = rr / w.runs;
+    const int64_t v = (int64_t)((z0 + dz) * w.XY) +
+                      64 * (int64_t)(rr - dz * w.runs) + (it & 63u);
+    const LinkSets ls = link_sets(w.f, w.X, w.Y, w.Z, v);
+    const uint32_t lc = kLink.ncomp[ls.lower], uc = kLink.ncomp[ls.upper];
+    const uint32_t c = on ? edge_count(lc, uc) : 0u;
+    uint32_t pre = 0, sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned long long b = lanes((c >> k) & 1u);
+      pre += __builtin_amdgcn_mbcnt_hi(
+                 (uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))
+             << k;
+      sum += (uint32_t)__popcll(b) << k;
+    }
+    if (on) egraph_emit(ls, v, w.X, w.XY, lc, uc, asc, desc, out, base + pre);
+    base += sum;
+  }
+}
+
+// The same graph with a word per 256 vertices in place of 20 bytes per run:
+// for grids whose planes are narrower than a run (chains along z), and for a
+// caller's workspace that holds no more.
+__global__ void __launch_bounds__(kBlock)
+k_egraph_count_small(const float *__restrict__ f, int64_t X, int64_t Y,
+                     int64_t Z, uint32_t *bcount, unsigned long long *ctr) {
   __shared__ uint32_t tmp[kBlock / 64];
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   uint32_t c = 0;
   bool nan = false;
   if (v < X * Y * Z) {
     const LinkSets ls = link_sets(f, X, Y, Z, v);
-    c = edge_count(ncomp[ls.lower], ncomp[ls.upper]);
+    c = edge_count(kLink.ncomp[ls.lower], kLink.ncomp[ls.upper]);
     nan = ls.nan;
   }
   flag_any(nan, ctr + kCtrNaN);
@@ -1760,67 +2012,59 @@ k_egraph_count(const float *__restrict__ f, int64_t X, int64_t Y, int64_t Z,
   if (threadIdx.x == 0) bcount[blockIdx.x] = tot;
 }
 
-// Edges of a vertex: ascending ones first, then descending; within a side,
-// components by increasing id of their extreme vertex (= neighbour order).
 __global__ void __launch_bounds__(kBlock)
-k_egraph_write(const float *__restrict__ f, int64_t X, int64_t Y, int64_t Z,
-               const uint8_t *__restrict__ ncomp,
-               const uint16_t *__restrict__ first,
-               const int32_t *__restrict__ asc,
-               const int32_t *__restrict__ desc,
-               const int64_t *__restrict__ boff, int32_t *__restrict__ out) {
+k_egraph_write_small(const float *__restrict__ f, int64_t X, int64_t Y,
+                     int64_t Z, const int32_t *__restrict__ asc,
+                     const int32_t *__restrict__ desc,
+                     const int64_t *__restrict__ boff,
+                     int32_t *__restrict__ out) {
   __shared__ uint32_t tmp[kBlock / 64];
   // A block without edges has nothing to write (the scan is block-local).
   if (boff[blockIdx.x + 1] == boff[blockIdx.x]) return;
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t XY = X * Y;
   LinkSets ls{};
   uint32_t lc = 0, uc = 0;
   if (v < X * Y * Z) {
     ls = link_sets(f, X, Y, Z, v);
-    lc = ncomp[ls.lower];
-    uc = ncomp[ls.upper];
+    lc = kLink.ncomp[ls.lower];
+    uc = kLink.ncomp[ls.upper];
   }
   const uint32_t c = edge_count(lc, uc);
   uint32_t tot = 0;
   const uint32_t ex = block_scan16(c, tmp, &tot);
-  if (!c) return;
-  int64_t at = boff[blockIdx.x] + ex;
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const bool high = side == 0;
-    const uint32_t set = high ? (uc >= 2 ? ls.upper : 0u)
-                              : (lc >= 2 ? ls.lower : 0u);
-    const uint32_t m = component_extremes(set, ls.fn, high, first);
-#pragma unroll
-    for (int i = 0; i < 14; ++i) {
-      if (!((m >> i) & 1u)) continue;
-      const int64_t u = v + kNb[i].dx + (int64_t)X * kNb[i].dy +
-                        XY * kNb[i].dz;
-      out[3 * at] = (int32_t)v;
-      out[3 * at + 1] = high ? asc[u] : desc[u];
-      out[3 * at + 2] = high ? 1 : -1;
-      ++at;
-    }
-  }
+  if (c)
+    egraph_emit(ls, v, X, X * Y, lc, uc, asc, desc, out,
+                boff[blockIdx.x] + ex);
+}
+
+// Planes per walk: 16 share the two extra planes and the staged table well;
+// fewer where the grid would not give each CU four blocks.
+Walk make_walk(const float *f, const int64_t *dims, unsigned *blocks) {
+  Walk w;
+  w.f = f;
+  w.X = (uint32_t)dims[0];
+  w.Y = (uint32_t)dims[1];
+  w.Z = (uint32_t)dims[2];
+  w.XY = w.X * w.Y;
+  w.runs = (w.XY + 63) / 64;
+  w.pb = (w.XY + kWalkThreads - 1) / kWalkThreads;
+  w.zc = 16;
+  while (w.zc > 2 && (uint64_t)w.pb * ((w.Z + w.zc - 1) / w.zc) < 1024)
+    w.zc /= 2;
+  *blocks = w.pb * ((w.Z + w.zc - 1) / w.zc);
+  return w;
 }
 
 }  // namespace
 
 int critical_points_run(msc_ctx *ctx, const float *field, const int64_t *dims,
                         uint8_t *code, hipStream_t s) {
-  const int64_t X = dims[0], Y = dims[1], Z = dims[2], N = X * Y * Z;
-  MSC_TRY(reserve(ctx, ctx->ws, align256(kLinkSets) + align256(2 * kLinkSets)));
-  Carver cv(ctx->ws);
-  uint8_t *ncomp = cv.take<uint8_t>(kLinkSets);
-  uint16_t *first = cv.take<uint16_t>(kLinkSets);
+  const int64_t N = dims[0] * dims[1] * dims[2];
+  unsigned nb = 0;
+  const Walk w = make_walk(field, dims, &nb);
   MSC_TRY(clear_counters(ctx, s));
-  MSC_PHASE(ctx, s, "link_tables", 3.0 * kLinkSets,
-            (k_link_tables<<<kLinkSets / kBlock, kBlock, 0, s>>>(ncomp,
-                                                                first)));
   MSC_PHASE(ctx, s, "critical", 5.0 * N,
-            (k_critical<<<grid64(N, kBlock), kBlock, 0, s>>>(
-                field, X, Y, Z, ncomp, code, ctx->dctr)));
+            (k_critical<<<nb, kWalkThreads, 0, s>>>(w, code, ctx->dctr)));
   MSC_TRY(read_counters(ctx, s));
   if (ctx->hctr[kCtrNaN]) return MSC_ENAN;
   ctx->stats = msc_stats{};
@@ -1832,36 +2076,51 @@ int extremum_graph_run(msc_ctx *ctx, const float *field, const int64_t *dims,
                        const int32_t *asc, const int32_t *desc, int32_t *edges,
                        int64_t capacity, int64_t *count, hipStream_t s) {
   const int64_t X = dims[0], Y = dims[1], Z = dims[2], N = X * Y * Z;
+  unsigned wb = 0;
+  const Walk w = make_walk(field, dims, &wb);
+  auto need = [](int64_t nc, bool marked) {
+    const int64_t nsb = (nc + kScan - 1) / kScan;
+    return align256(nc * 4) + align256((nc + 1) * 8) + align256(nsb * 8 + 8) +
+           (marked ? align256(nc * 8) : 0) + 4096;
+  };
   const int64_t nb = (N + kBlock - 1) / kBlock;
-  const int64_t nsb = (nb + kScan - 1) / kScan;
-  MSC_TRY(reserve(ctx, ctx->ws, align256(nb * 4) + align256((nb + 1) * 8) +
-                               align256(nsb * 8 + 8) + align256(kLinkSets) +
-                               align256(2 * kLinkSets) + 4096));
+  const int64_t runs = (int64_t)w.runs * Z;
+  const bool marked = w.XY >= 64 && !(ctx->ws.external &&
+                                      ctx->ws.bytes < need(runs, true));
+  // Edge counts per run, or per block of 256 vertices.
+  const int64_t nc = marked ? runs : nb;
+  MSC_TRY(reserve(ctx, ctx->ws, need(nc, marked)));
   Carver cv(ctx->ws);
-  uint32_t *bcount = cv.take<uint32_t>(nb);
-  int64_t *boff = cv.take<int64_t>(nb + 1);
-  uint64_t *bsum = cv.take<uint64_t>(nsb + 1);
-  uint8_t *ncomp = cv.take<uint8_t>(kLinkSets);
-  uint16_t *first = cv.take<uint16_t>(kLinkSets);
+  uint32_t *cnt = cv.take<uint32_t>(nc);
+  int64_t *off = cv.take<int64_t>(nc + 1);
+  uint64_t *bsum = cv.take<uint64_t>((nc + kScan - 1) / kScan + 1);
+  unsigned long long *marks =
+      marked ? cv.take<unsigned long long>(nc) : nullptr;
   MSC_TRY(clear_counters(ctx, s));
-  MSC_PHASE(ctx, s, "link_tables", 3.0 * kLinkSets,
-            (k_link_tables<<<kLinkSets / kBlock, kBlock, 0, s>>>(ncomp,
-                                                                first)));
-  MSC_PHASE(ctx, s, "egraph_count", 4.0 * N,
-            (k_egraph_count<<<(unsigned)nb, kBlock, 0, s>>>(
-                 field, X, Y, Z, ncomp, bcount, ctx->dctr),
-             scan64(ctx, bcount, nb, boff, bsum, s)));
+  MSC_PHASE(
+      ctx, s, "egraph_count", 4.0 * N,
+      (marked ? k_egraph_mark<<<wb, kWalkThreads, 0, s>>>(w, marks, cnt,
+                                                          ctx->dctr)
+              : k_egraph_count_small<<<(unsigned)nb, kBlock, 0, s>>>(
+                    field, X, Y, Z, cnt, ctx->dctr),
+       scan64(ctx, cnt, nc, off, bsum, s)));
   int64_t total = 0;
-  MSC_HIP_TRY(hipMemcpyAsync(&total, boff + nb, sizeof(int64_t),
+  MSC_HIP_TRY(hipMemcpyAsync(&total, off + nc, sizeof(int64_t),
                              hipMemcpyDeviceToHost, s));
   MSC_TRY(read_counters(ctx, s));
   if (ctx->hctr[kCtrNaN]) return MSC_ENAN;
   *count = total;
-  if (edges && capacity >= total && total > 0)
+  if (edges && capacity >= total && total > 0) {
+    // Runs per wave: as many as hold about 32 edges.
+    const int K = (int)std::min<int64_t>(64, std::max<int64_t>(1, 32 * nc / total));
     MSC_PHASE(ctx, s, "egraph_write", 4.0 * N + 12.0 * total,
-              (k_egraph_write<<<(unsigned)nb, kBlock, 0, s>>>(
-                  field, X, Y, Z, ncomp, first, asc, desc, boff, edges)));
-  MSC_TRY(read_counters(ctx, s));
+              (marked ? k_egraph_write<<<grid64((nc + K - 1) / K * 64, kBlock),
+                                         kBlock, 0, s>>>(
+                            w, (uint64_t)nc, K, marks, off, asc, desc, edges)
+                      : k_egraph_write_small<<<(unsigned)nb, kBlock, 0, s>>>(
+                            field, X, Y, Z, asc, desc, off, edges)));
+    MSC_TRY(read_counters(ctx, s));
+  }
   ctx->stats = msc_stats{};
   ctx->stats.n_vertices = N;
   return MSC_OK;

@@ -90,3 +90,28 @@ def test_fullsize_sampled(msc):
         bx, by = box.shape[2], box.shape[1]
         k = (x - x0) + bx * (y - y0) + bx * by * (z - z0)
         assert (ch[v] & 15, ch[v] >> 4) == (bl[k], bu[k]), int(v)
+
+
+@pytest.mark.parametrize("dims", [(64, 1, 9), (8, 8, 17), (7, 9, 21),
+                                  (63, 5, 3), (65, 16, 2), (513, 1, 5),
+                                  (1, 1, 300), (20, 26, 33), (300, 200, 1)])
+@pytest.mark.parametrize("kind", ["noise", "smooth"])
+def test_runs_and_walks(msc, dims, kind):
+    """Around the 64 positions of a run, the 512 of a block and the planes of
+    a walk, planes narrower than a run, with nearly every vertex marked and
+    with few; and again from a workspace without room for the marks."""
+    f = (synth.random_field(dims, seed=9) if kind == "noise" else
+         synth.perlin_field(dims, seed=9, frequency=0.15))
+    _, E = check(msc, f, f"{dims} {kind}")
+    t = torch.from_numpy(np.ascontiguousarray(f)).cuda()
+    a, d, _ = msc.segment(t)
+    torch.cuda.synchronize()
+    nb = (f.size + 255) // 256
+    small = torch.empty(4 * nb + 8 * (nb + 1) + 8192, dtype=torch.uint8,
+                        device="cuda")
+    try:
+        msc.set_workspace(small)
+        again = msc.extremum_graph(t, a, d).cpu().numpy()
+    finally:
+        msc.set_workspace(None)
+    np.testing.assert_array_equal(again, E, err_msg=f"{dims} small workspace")
