@@ -49,6 +49,7 @@ constexpr int kBlock = 256;
 // Slots of the small device counter block each context owns.
 enum Counter : int {
   kCtrChanged = 0,   // set nonzero by a round that changed something
+  kCtrGiant = 1,     // CSR components: the root most of a sample has (32 bits)
   kCtrExits = 5,     // exits over all tiles (from the scan)
   kCtrBadIndex = 6,  // out-of-range CSR column seen
   kCtrOverflow = 7,  // pair table full (bit 0), broken exit chain (bit 1),

@@ -226,3 +226,33 @@ def test_batched_masks_edge_cases(msc):
     (lab,) = msc.cc_label_grid_batched([m])
     torch.cuda.synchronize()
     assert (lab == 0).all()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 65, 4095, 4096, 4097, 8191, 8192,
+                               8193, 100003])
+@pytest.mark.parametrize("deg", [0.6, 2.5])
+@pytest.mark.parametrize("both", [False, True])
+def test_csr_sizes(msc, n, deg, both):
+    """Random graphs around the sizes where the passes change, without and
+    with a large component, each edge listed once or twice, in no order, with
+    self-loops; unmasked, half masked and nearly unmasked."""
+    rng = np.random.default_rng(n + int(10 * deg))
+    E = rng.integers(0, n, size=(int(n * deg), 2))
+    if both:
+        E = np.concatenate([E, E[:, ::-1]])
+    E = E[rng.permutation(len(E))]
+    order = np.argsort(E[:, 0], kind="stable")
+    row_ptr = np.zeros(n + 1, np.int64)
+    row_ptr[1:] = np.cumsum(np.bincount(E[:, 0], minlength=n))
+    col = np.ascontiguousarray(E[order, 1].astype(np.int32))
+    for share in (None, 0.5, 0.01):
+        mask = None if share is None else (
+            rng.uniform(size=n) < share).astype(np.uint8)
+        want, _ = O.cc_csr(row_ptr, col, mask)
+        np.testing.assert_array_equal(
+            gpu_cc_csr(msc, row_ptr, col, mask), want, err_msg=str(share))
+    if col.size:
+        col[col.size // 2] = n
+        with pytest.raises(msc.MscError) as e:
+            gpu_cc_csr(msc, row_ptr, col)
+        assert e.value.code == msc.MSC_EINVAL
