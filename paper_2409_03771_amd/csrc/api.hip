@@ -112,10 +112,13 @@ int slot_copied(msc_ctx *ctx, int slot, hipStream_t s) {
   return MSC_OK;
 }
 
-int read_counters(msc_ctx *ctx, hipStream_t stream) {
+int read_counters(msc_ctx *ctx, hipStream_t stream, const void *extra) {
   MSC_HIP_TRY(hipMemcpyAsync(ctx->hctr, ctx->dctr,
                              kNumCounters * sizeof(unsigned long long),
                              hipMemcpyDeviceToHost, stream));
+  if (extra)
+    MSC_HIP_TRY(hipMemcpyAsync(ctx->hctr + kCtrExtra, extra, 8,
+                               hipMemcpyDeviceToHost, stream));
   MSC_HIP_TRY(hipStreamSynchronize(stream));
   if (ctx->prof.on) ctx->prof.flush();
   return MSC_OK;

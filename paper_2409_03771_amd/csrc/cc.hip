@@ -1731,17 +1731,16 @@ int csr_from_tets_run(msc_ctx *ctx, int64_t n, int64_t ntets,
                   n, off, cand, cnt, col_idx != nullptr)));
   MSC_PHASE(ctx, s, "rows_scan", 12.0 * n,
             (scan64(ctx, cnt, n, row_ptr, bsum, s)));
-  int64_t total = 0;
-  MSC_HIP_TRY(hipMemcpyAsync(&total, row_ptr + n, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, s));
-  MSC_TRY(read_counters(ctx, s));
+  MSC_TRY(read_counters(ctx, s, row_ptr + n));
   if (ctx->hctr[kCtrBadIndex]) return MSC_EINVAL;
+  const int64_t total = (int64_t)ctx->hctr[kCtrExtra];
   *nnz = total;
-  if (col_idx && capacity >= total && total > 0)
+  if (col_idx && capacity >= total && total > 0) {
     MSC_PHASE(ctx, s, "rows_fill", 4.0 * ncand + 4.0 * total,
               (k_row_fill<<<grid64(n, kRows), kRows, 0, s>>>(
                   n, off, cand, row_ptr, col_idx)));
-  MSC_TRY(read_counters(ctx, s));
+    MSC_TRY(read_counters(ctx, s));
+  }
   ctx->stats = msc_stats{};
   ctx->stats.n_vertices = n;
   return MSC_OK;
@@ -2316,11 +2315,9 @@ int extremum_graph_run(msc_ctx *ctx, const float *field, const int64_t *dims,
               : k_egraph_count_small<<<(unsigned)nb, kBlock, 0, s>>>(
                     field, X, Y, Z, cnt, ctx->dctr),
        scan64(ctx, cnt, nc, off, bsum, s)));
-  int64_t total = 0;
-  MSC_HIP_TRY(hipMemcpyAsync(&total, off + nc, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, s));
-  MSC_TRY(read_counters(ctx, s));
+  MSC_TRY(read_counters(ctx, s, off + nc));
   if (ctx->hctr[kCtrNaN]) return MSC_ENAN;
+  const int64_t total = (int64_t)ctx->hctr[kCtrExtra];
   *count = total;
   if (edges && capacity >= total && total > 0) {
     // Runs per wave: as many as hold about 32 edges.

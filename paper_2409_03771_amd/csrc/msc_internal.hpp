@@ -50,6 +50,7 @@ constexpr int kBlock = 256;
 enum Counter : int {
   kCtrChanged = 0,   // set nonzero by a round that changed something
   kCtrGiant = 1,     // CSR components: the root most of a sample has (32 bits)
+  kCtrCells = 2,     // vertices that are their own cell label
   kCtrExits = 5,     // exits over all tiles (from the scan)
   kCtrBadIndex = 6,  // out-of-range CSR column seen
   kCtrOverflow = 7,  // pair table full (bit 0), broken exit chain (bit 1),
@@ -60,6 +61,7 @@ enum Counter : int {
   kCtrRootsMax = 11, // vertices that are their own ascent label
   kCtrRootsMin = 12, // vertices that are their own descent label
   kCtrNaN = 13,      // a NaN field value seen (CSR segmentation)
+  kCtrExtra = 15,    // host side only: a value read back with the counters
   kNumCounters = 16
 };
 
@@ -252,7 +254,9 @@ struct Carver {
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Read the counter block back to the host (synchronises `stream`).
-int read_counters(msc_ctx *ctx, hipStream_t stream);
+// (`extra`: a device value of 8 bytes that comes back as hctr[kCtrExtra]).
+int read_counters(msc_ctx *ctx, hipStream_t stream,
+                  const void *extra = nullptr);
 int clear_counters(msc_ctx *ctx, hipStream_t stream);
 // Zero n counters with a kernel on `stream`.
 int zero_u64(unsigned long long *p, int n, hipStream_t stream);

@@ -1407,7 +1407,9 @@ __global__ void k_table_clear(unsigned long long *keys, int32_t *vals,
 constexpr uint32_t kTableProbes = 512;
 
 // Insert (key, id) keeping the smallest id; reads before each atomic so that
-// the common case (key present with a smaller id) stays a plain load.
+// the common case (key present with a smaller id) stays a plain load.  The
+// reads may come from a cache: a slot's key never changes once it is there, a
+// slot that seems empty is claimed by an atomic, and an older value is larger.
 __device__ __forceinline__ bool table_insert(unsigned long long *keys,
                                              int32_t *vals, uint32_t mask,
                                              unsigned long long key,
@@ -1415,7 +1417,8 @@ __device__ __forceinline__ bool table_insert(unsigned long long *keys,
   uint32_t h = (uint32_t)mix64(key) & mask;
 #pragma unroll 1
   for (uint32_t probe = 0; probe <= mask && probe < kTableProbes; ++probe) {
-    unsigned long long cur = __atomic_load_n(&keys[h], __ATOMIC_RELAXED);
+    unsigned long long cur = __hip_atomic_load(
+        &keys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (cur == kEmptyKey) {
       cur = atomicCAS(&keys[h], kEmptyKey, key);
       if (cur == kEmptyKey) {
@@ -1424,7 +1427,8 @@ __device__ __forceinline__ bool table_insert(unsigned long long *keys,
       }
     }
     if (cur == key) {
-      if (__atomic_load_n(&vals[h], __ATOMIC_RELAXED) > id)
+      if (__hip_atomic_load(&vals[h], __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_WORKGROUP) > id)
         atomicMin(&vals[h], id);
       return true;
     }
@@ -2621,14 +2625,16 @@ k_rank_relabel(RankGeo g, const SlabDev *__restrict__ slabs,
   }
 }
 
+// Sums of the blocks' two counts, added to *ca and (unless NULL) *cd.
 __global__ void __launch_bounds__(1024)
 k_rank_roots_sum(const uint32_t *__restrict__ roots, uint32_t nb,
-                 unsigned long long *ctr) {
+                 unsigned long long *ca, unsigned long long *cd) {
   __shared__ unsigned long long sa[16], sd[16];
   unsigned long long a = 0, d = 0;
-  for (uint32_t i = threadIdx.x; i < nb; i += 1024) {
-    a += roots[2 * i];
-    d += roots[2 * i + 1];
+  for (uint32_t i = blockIdx.x * 1024 + threadIdx.x; i < nb;
+       i += gridDim.x * 1024) {
+    a += roots[2 * (size_t)i];
+    d += roots[2 * (size_t)i + 1];
   }
   for (int o = 32; o > 0; o >>= 1) {
     a += __shfl_xor(a, o);
@@ -2644,26 +2650,58 @@ k_rank_roots_sum(const uint32_t *__restrict__ roots, uint32_t nb,
       a += sa[w];
       d += sd[w];
     }
-    ctr[kCtrRootsMax] = a;
-    ctr[kCtrRootsMin] = d;
+    if (a) atomicAdd(ca, a);
+    if (d && cd) atomicAdd(cd, d);
   }
 }
 
-// Cells over final labels: the smallest id of every (asc, desc) pair.  A
-// lane whose pair equals the previous lane's (one id smaller) is not its
-// pair's smallest id and inserts nothing; a run of equal pairs inserts once.
+inline unsigned sum_grid(uint64_t nb) {
+  return (unsigned)std::min<uint64_t>(32, (nb + 1023) / 1024);
+}
+
+// Cells over final labels in no spatial order: the smallest id of every
+// (asc, desc) pair.  A block takes `per` consecutive runs of kBlock vertices
+// through an LDS table of their distinct pairs, so a cell that fills much of
+// the mesh costs one insert per block; with one per vertex they queue up on the
+// large cells' slots (9M vertices: 0.65 ms, 0.13 this way; 1M: a whole call 0.85 and 0.48).
 __global__ void __launch_bounds__(kBlock)
-k_rank_pairs(uint64_t n, const int32_t *__restrict__ asc,
-             const int32_t *__restrict__ desc, unsigned long long *keys,
-             int32_t *vals, uint32_t mask, unsigned long long *ctr) {
-  const uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool in = v < n;
-  const unsigned long long key = in ? pair_key(asc[v], desc[v]) : kEmptyKey;
-  const unsigned long long left = __shfl_up(key, 1);
-  const bool start = (threadIdx.x & 63) == 0 || key != left;
+k_csr_pairs(uint64_t n, int per, const int32_t *__restrict__ asc,
+            const int32_t *__restrict__ desc, unsigned long long *keys,
+            int32_t *vals, uint32_t mask, unsigned long long *ctr) {
+  constexpr int K = kPairSlots / kBlock;
+  __shared__ unsigned long long skey[kPairSlots];
+  __shared__ int32_t sval[kPairSlots];
+  __shared__ unsigned sfill;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < kPairSlots; i += kBlock) {
+    skey[i] = kEmptyKey;
+    sval[i] = INT32_MAX;
+  }
+  if (tid == 0) sfill = 0;
+  __syncthreads();
   unsigned fresh = 0;
   bool ok = true;
-  if (in && start) ok = table_insert(keys, vals, mask, key, (int32_t)v, &fresh);
+  const uint64_t v0 = (uint64_t)blockIdx.x * per * kBlock + tid;
+  for (int k = 0; k < per; ++k) {
+    const uint64_t v = v0 + (uint64_t)k * kBlock;
+    if (v >= n) break;
+    const unsigned long long key = pair_key(asc[v], desc[v]);
+    const int slot = pair_slot(skey, &sfill, key);
+    if (slot >= 0)
+      atomicMin(&sval[slot], (int32_t)v);
+    else
+      ok &= table_insert(keys, vals, mask, key, (int32_t)v, &fresh);
+  }
+  __syncthreads();
+  unsigned long long key[K];
+  int32_t id[K];
+  uint32_t at[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    key[k] = skey[tid + k * kBlock];
+    id[k] = sval[tid + k * kBlock];
+  }
+  ok &= table_insert_many<K>(keys, vals, mask, key, id, at, &fresh);
   if (!ok) atomicOr(ctr + kCtrOverflow, 1ull);
 }
 
@@ -2932,8 +2970,9 @@ int segment_ranks(msc_ctx *ctx, const float *field, const int64_t dims[3],
   MSC_PHASE(ctx, s, "rank_relabel", 16.0 * N,
             (k_rank_relabel<<<rgrid, kBlock, 0, s>>>(rg, dsl, A, D, FA, FD, fa,
                                                     fd, roots),
-             k_rank_roots_sum<<<1, 1024, 0, s>>>(roots, rgrid.x * rgrid.y,
-                                                 ctx->dctr)));
+             k_rank_roots_sum<<<sum_grid(rgrid.x * rgrid.y), 1024, 0, s>>>(
+                 roots, rgrid.x * rgrid.y, ctx->dctr + kCtrRootsMax,
+                 ctx->dctr + kCtrRootsMin)));
   MSC_TRY(read_counters(ctx, s));
   const uint64_t nmax = ctx->hctr[kCtrRootsMax], nmin = ctx->hctr[kCtrRootsMin];
   int64_t cells = -1;
@@ -2953,10 +2992,11 @@ int segment_ranks(msc_ctx *ctx, const float *field, const int64_t dims[3],
               (k_rank_tile_ms<<<ntile, kBlock, 0, s>>>(
                    X, Y, Z, fa, fd, keys, vals, (uint32_t)(cap - 1), ms,
                    roots),
-               k_rank_roots_sum<<<1, 1024, 0, s>>>(roots, ntile, ctx->dctr)));
+               k_rank_roots_sum<<<sum_grid(ntile), 1024, 0, s>>>(
+                   roots, ntile, ctx->dctr + kCtrCells, nullptr)));
     MSC_TRY(read_counters(ctx, s));
     if (ctx->hctr[kCtrOverflow]) return MSC_ENOMEM;
-    cells = (int64_t)ctx->hctr[kCtrRootsMax];
+    cells = (int64_t)ctx->hctr[kCtrCells];
   }
   ctx->stats = msc_stats{};
   ctx->stats.n_vertices = (int64_t)N;
@@ -2993,7 +3033,7 @@ constexpr int kRowChunk = 8;  // column entries gathered per round trip
 // reported); NaN values lose every comparison and are reported.  Each block
 // counts its extrema (vertices that are their own successor).
 __global__ void __launch_bounds__(kBlock)
-k_csr_steepest(int64_t n, int64_t nnz, const int64_t *__restrict__ rp,
+k_csr_steepest(int64_t n, const int64_t *__restrict__ rp,
                const int32_t *__restrict__ col, const float *__restrict__ f,
                int32_t *__restrict__ sp, int32_t *__restrict__ sm,
                uint32_t *__restrict__ counts, unsigned long long *ctr) {
@@ -3001,7 +3041,8 @@ k_csr_steepest(int64_t n, int64_t nnz, const int64_t *__restrict__ rp,
   if (threadIdx.x == 0) s_max = s_min = 0;
   __syncthreads();
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  bool bad = false, nan = false, is_max = false, is_min = false;
+  const int64_t nnz = rp[n];
+  bool bad = nnz < 0, nan = false, is_max = false, is_min = false;
   if (v < n) {
     const float fv = f[v];
     nan = fv != fv;
@@ -3061,52 +3102,69 @@ k_csr_steepest(int64_t n, int64_t nnz, const int64_t *__restrict__ rp,
   }
 }
 
-// Root of v in a successor forest, compressing as it goes (path halving:
-// an entry only ever moves to an ancestor, so concurrent chases agree).
-// Successors climb the (f, id) order strictly, so every chase ends.
-__device__ __forceinline__ int32_t chase_halving(int32_t *S, int32_t x) {
-  for (;;) {
-    const int32_t p = __atomic_load_n(&S[x], __ATOMIC_RELAXED);
-    if (p == x) return x;
-    const int32_t g = __atomic_load_n(&S[p], __ATOMIC_RELAXED);
-    if (g == p) return p;
-    __atomic_store_n(&S[x], g, __ATOMIC_RELAXED);
-    x = g;
-  }
+// Path halving along both of a vertex's chases, side by side (the cost is the
+// gathers' latency and rate; one after the other, at system scope, 208^3
+// vertices took 1.77 ms, this way 1.56).  An entry only ever moves to an
+// ancestor and successors climb the (f, id) order strictly, so concurrent
+// chases agree and end, also on the older values that a cached load returns.
+// No final value is written: a halving store may land after another thread's,
+// so a root written here could be overwritten by an older ancestor.
+__device__ __forceinline__ int32_t ld_near(const int32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// First pass: every vertex chases its root with path halving, which
-// shortens every path but writes no final value -- a halving store may land
-// after another thread's, so a root written here could be overwritten by an
-// older ancestor.
 __global__ void __launch_bounds__(kBlock)
 k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (v >= n) return;
-  (void)chase_halving(A, (int32_t)v);
-  (void)chase_halving(D, (int32_t)v);
-}
-
-// Root of x without writing (every value read is an ancestor of x).
-__device__ __forceinline__ int32_t walk_root(const int32_t *S, int32_t x) {
-  for (;;) {
-    const int32_t p = __hip_atomic_load(&S[x], __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (p == x) return x;
-    x = p;
+  int32_t xa = (int32_t)v, xd = (int32_t)v;
+  bool ea = false, ed = false;
+  while (!(ea && ed)) {
+    // A chase that has ended reloads its last entries harmlessly.
+    const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
+    const int32_t ga = ld_near(&A[pa]), gd = ld_near(&D[pd]);
+    if (!ea) {
+      ea = ga == pa;
+      if (!ea) {
+        __hip_atomic_store(&A[xa], ga, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        xa = ga;
+      }
+    }
+    if (!ed) {
+      ed = gd == pd;
+      if (!ed) {
+        __hip_atomic_store(&D[xd], gd, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        xd = gd;
+      }
+    }
   }
 }
 
-// Second pass: only the owner writes an entry, and it writes the root, so a
-// concurrent reader sees the old pointer or the root, both ancestors.
+// Every vertex walks up both forests to its roots and writes its own two
+// entries: only the owner writes an entry, so a concurrent reader sees the old
+// pointer or the root, both ancestors, and a walk that meets a vertex that is
+// done ends there.  Up to kWalkOnly vertices that alone is enough: a walk meets
+// a finished vertex within ten steps once a tenth are done, and the halving
+// stores cost more than the steps they save (100^3: 0.92 ms a call instead of
+// 1.21; 208^3, where the gathers miss the caches: 1.83 ms against 1.71 for
+// both passes).
+constexpr int64_t kWalkOnly = 1 << 22;
+
 __global__ void __launch_bounds__(kBlock)
 k_csr_roots(int64_t n, int32_t *A, int32_t *D) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (v >= n) return;
-  const int32_t a = walk_root(A, (int32_t)v);
-  const int32_t d = walk_root(D, (int32_t)v);
-  __hip_atomic_store(&A[v], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&D[v], d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int32_t xa = (int32_t)v, xd = (int32_t)v;
+  for (;;) {
+    const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
+    if (pa == xa && pd == xd) break;
+    xa = pa;  // a walk that has ended reloads its root harmlessly
+    xd = pd;
+  }
+  __hip_atomic_store(&A[v], xa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&D[v], xd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -3120,13 +3178,15 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
     return MSC_OK;
   }
   const uint32_t nblk = (uint32_t)((n + kBlock - 1) / kBlock);
-  // Edge count, for the pass's algorithmic bytes (row pointer, column index
-  // and the neighbour's value per entry).
+  // The entry count is read where it decides something here: whether there may
+  // be no column array, and the traced pass's bytes.
   int64_t nnz = 0;
-  MSC_HIP_TRY(hipMemcpyAsync(&nnz, row_ptr + n, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, s));
-  MSC_HIP_TRY(hipStreamSynchronize(s));
-  if (nnz < 0 || (nnz > 0 && !col_idx)) return MSC_EINVAL;
+  if (!col_idx || ctx->prof.on) {
+    MSC_HIP_TRY(hipMemcpyAsync(&nnz, row_ptr + n, sizeof(int64_t),
+                               hipMemcpyDeviceToHost, s));
+    MSC_HIP_TRY(hipStreamSynchronize(s));
+    if (nnz < 0 || (nnz > 0 && !col_idx)) return MSC_EINVAL;
+  }
   MSC_TRY(reserve(ctx, ctx->rk, 2 * align256((uint64_t)n * 4) +
                                align256(nblk * 8ull) + 4096));
   Carver cv(ctx->rk);
@@ -3135,24 +3195,34 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   int32_t *D = desc ? desc : cv.take<int32_t>(n);
   MSC_TRY(clear_counters(ctx, s));
   MSC_PHASE(ctx, s, "csr_steepest", 20.0 * n + 8.0 * (double)nnz,
-            (k_csr_steepest<<<nblk, kBlock, 0, s>>>(n, nnz, row_ptr, col_idx,
-                                                    field,
+            (k_csr_steepest<<<nblk, kBlock, 0, s>>>(n, row_ptr, col_idx, field,
                                                     A, D, roots, ctx->dctr),
-             k_rank_roots_sum<<<1, 1024, 0, s>>>(roots, nblk, ctx->dctr)));
-  MSC_PHASE(ctx, s, "csr_compress", 16.0 * n,
-            (k_csr_compress<<<nblk, kBlock, 0, s>>>(n, A, D),
-             k_csr_roots<<<nblk, kBlock, 0, s>>>(n, A, D)));
-  MSC_TRY(read_counters(ctx, s));
-  if (ctx->hctr[kCtrBadIndex]) return MSC_EINVAL;
-  if (ctx->hctr[kCtrNaN]) return MSC_ENAN;
+             k_rank_roots_sum<<<sum_grid(nblk), 1024, 0, s>>>(
+                 roots, nblk, ctx->dctr + kCtrRootsMax,
+                 ctx->dctr + kCtrRootsMin)));
+  // The extremum counts come back while the compression runs.
+  MSC_HIP_TRY(hipMemcpyAsync(ctx->hctr, ctx->dctr, kNumCounters * 8,
+                             hipMemcpyDeviceToHost, s));
+  MSC_HIP_TRY(hipEventRecord(ctx->done, s));
+  if (n > kWalkOnly)
+    MSC_PHASE(ctx, s, "csr_compress", 16.0 * n,
+              (k_csr_compress<<<nblk, kBlock, 0, s>>>(n, A, D)));
+  MSC_PHASE(ctx, s, "csr_roots", 16.0 * n,
+            (k_csr_roots<<<nblk, kBlock, 0, s>>>(n, A, D)));
+  MSC_HIP_TRY(hipEventSynchronize(ctx->done));
   const uint64_t nmax = ctx->hctr[kCtrRootsMax], nmin = ctx->hctr[kCtrRootsMin];
+  const bool bad = ctx->hctr[kCtrBadIndex], nan = ctx->hctr[kCtrNaN];
   int64_t cells = -1;
-  if (ms) {
+  if (ms && !bad && !nan) {
     // Pair table: first capacity from the extremum counts, grown fourfold
-    // while the pair pass overflows.
+    // while the pair pass overflows.  The cell pass is queued behind it
+    // without a look at the outcome; after an overflow both run again.
     uint64_t cap = table_first_capacity((uint64_t)n, nmax, nmin,
                                         ctx->table_first);
     const uint64_t full = table_capacity((uint64_t)n, nmax, nmin);
+    // 16 runs per block, fewer where that would leave CUs without one.
+    const int per = (int)std::min<uint32_t>(16, std::max(1u, nblk / 1024));
+    const uint32_t pblk = (nblk + per - 1) / per;
     for (;;) {
       MSC_TRY(reserve(ctx, ctx->tab, align256(cap * 8) + align256(cap * 4) + 4096));
       Carver tc(ctx->tab);
@@ -3161,26 +3231,30 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
       MSC_PHASE(ctx, s, "csr_pairs", 12.0 * n,
                 (k_table_clear<<<(unsigned)((cap + kBlock - 1) / kBlock),
                                  kBlock, 0, s>>>(keys, vals, cap),
-                 k_rank_pairs<<<nblk, kBlock, 0, s>>>((uint64_t)n, A, D, keys,
-                                                      vals, (uint32_t)(cap - 1),
-                                                      ctx->dctr)));
+                 k_csr_pairs<<<pblk, kBlock, 0, s>>>(
+                     (uint64_t)n, per, A, D, keys, vals, (uint32_t)(cap - 1),
+                     ctx->dctr)));
+      MSC_PHASE(ctx, s, "csr_ms", 12.0 * n,
+                (k_rank_ms<<<nblk, kBlock, 0, s>>>(
+                     (uint64_t)n, A, D, keys, vals, (uint32_t)(cap - 1), ms,
+                     roots),
+                 k_rank_roots_sum<<<sum_grid(nblk), 1024, 0, s>>>(
+                     roots, nblk, ctx->dctr + kCtrCells, nullptr)));
       MSC_TRY(read_counters(ctx, s));
       if (!ctx->hctr[kCtrOverflow]) {
-        MSC_PHASE(ctx, s, "csr_ms", 12.0 * n,
-                  (k_rank_ms<<<nblk, kBlock, 0, s>>>(
-                       (uint64_t)n, A, D, keys, vals, (uint32_t)(cap - 1), ms,
-                       roots),
-                   k_rank_roots_sum<<<1, 1024, 0, s>>>(roots, nblk,
-                                                       ctx->dctr)));
-        MSC_TRY(read_counters(ctx, s));
-        cells = (int64_t)ctx->hctr[kCtrRootsMax];
+        cells = (int64_t)ctx->hctr[kCtrCells];
         break;
       }
       if (cap >= full) return MSC_ENOMEM;
       cap = cap * 4 < full ? cap * 4 : full;
       k_fill_u64<<<1, kBlock, 0, s>>>(ctx->dctr + kCtrOverflow, 1, 0ull);
+      k_fill_u64<<<1, kBlock, 0, s>>>(ctx->dctr + kCtrCells, 1, 0ull);
     }
+  } else {
+    MSC_TRY(read_counters(ctx, s));
   }
+  if (bad) return MSC_EINVAL;
+  if (nan) return MSC_ENAN;
   ctx->stats = msc_stats{};
   ctx->stats.n_vertices = n;
   ctx->stats.n_maxima = (int64_t)nmax;

@@ -144,3 +144,33 @@ def test_pair_table_regrows(msc):
         assert msc.last_stats()["n_cells"] > 4096
     finally:
         msc.set_table_capacity(0)
+
+
+@pytest.mark.parametrize("X,Y", [(256, 1), (257, 3), (800, 700), (2100, 2100)])
+@pytest.mark.parametrize("kind", ["noise", "smooth"])
+def test_sizes_against_the_grid(msc, X, Y, kind):
+    """Sizes on both sides of where a block takes several runs of vertices and
+    where paths are halved first: on a plane's own adjacency the labels are
+    those of the plane (whose path has tests of its own)."""
+    f = (synth.random_field((X, Y, 1), seed=3) if kind == "noise" else
+         synth.perlin_field((X, Y, 1), seed=3, frequency=0.07))
+    n = X * Y
+    y, x = np.divmod(np.arange(n), X)
+    nbr, ok = [], []
+    for dx, dy in ((-1, -1), (0, -1), (-1, 0), (1, 0), (0, 1), (1, 1)):
+        ok.append((x + dx >= 0) & (x + dx < X) & (y + dy >= 0) & (y + dy < Y))
+        nbr.append(np.arange(n) + dx + X * dy)
+    ok, nbr = np.stack(ok, 1), np.stack(nbr, 1)
+    rp = np.zeros(n + 1, np.int64)
+    rp[1:] = np.cumsum(ok.sum(1))
+    t = torch.from_numpy(np.ascontiguousarray(f)).cuda()
+    got = msc.segment_csr(torch.from_numpy(rp).cuda(),
+                          torch.from_numpy(nbr[ok].astype(np.int32)).cuda(),
+                          t.reshape(-1))
+    st = msc.last_stats()
+    want = msc.segment(t)
+    for name, g, w in zip(("asc", "desc", "ms"), got, want):
+        assert torch.equal(g, w), name
+    wt = msc.last_stats()
+    for k in ("n_maxima", "n_minima", "n_cells"):
+        assert st[k] == wt[k], k
