@@ -12,14 +12,14 @@
 //
 // Grid masks use the same two levels as the segmentation, mirroring the
 // paper's rank-local pass plus exchange:
-//   cc_tile    one workgroup per tile: union-find over the tile's own edges
-//              in LDS; writes each vertex's tile-local root (16-bit) and
-//              makes every tile-local root its own parent in the global
-//              label array;
+//   cc_tile    one workgroup per tile, one thread per row: union-find in LDS
+//              over the rows' runs of masked vertices; writes the rows as bits
+//              and each run's tile-local root (16-bit), and makes every
+//              tile-local root its own parent in the global label array;
 //   cc_cross   unions across the tile faces (each cross-tile edge once, from
 //              the tile holding its lower endpoint) on the global array,
 //              touching tile-local roots only (the paper's ghost exchange);
-//   cc_final   label = root of the vertex's tile-local root.
+//   cc_final   label = root of the vertex's run's tile-local root.
 // CSR graphs have no locality to exploit: hooks to a smaller masked neighbour,
 // unions along the listed edges, then a final find per vertex.
 #include <algorithm>
@@ -157,10 +157,9 @@ __device__ __forceinline__ void uf_unite_dev(T *par, T a, T b) {
 // Grid masks
 // ---------------------------------------------------------------------------
 
-constexpr int CTX = 32, CTY = 16, CTZ = 16;      // tile; one thread per column
-constexpr int kCThreads = CTX * CTY;
+constexpr int CTX = 32, CTY = 16, CTZ = 16;      // tile
+constexpr int kCThreads = CTX * CTY;             // the label pass: one per column
 constexpr int kCOwned = CTX * CTY * CTZ;
-constexpr uint16_t kOutside = 0xffff;           // unmasked vertex
 static_assert(kCOwned < 65535, "tile-local roots are 16-bit");
 
 struct CGeo {
@@ -184,11 +183,36 @@ __device__ __forceinline__ CTile ctile_at(const CGeo &g, int64_t t) {
   return CTile{tx * CTX, ty * CTY, tz * CTZ};
 }
 
-// The tile-local roots are stored tile-major: tile t's kCOwned entries,
-// indexed by the tile-local index, are one contiguous run, so the passes
-// read and write whole runs instead of a row of CTX entries per (y, z).
-__device__ __forceinline__ int64_t loc_index(int64_t t, int l) {
-  return t * kCOwned + l;
+// What a tile's own pass leaves for the other two, in the tile's slot of the
+// workspace (kCOwned 16-bit words, of which 6.5 KB stay unused): its
+// rows as 32-bit masks, the number of each row's first run, and for every run
+// (consecutive masked x of a row, numbered in index order) the local index of
+// its component's first vertex.  A row is CTX vertices; row r = ly + CTY*lz.
+constexpr int kCRows = CTY * CTZ;
+constexpr int kCRuns = kCRows * (CTX / 2);  // at most 16 runs in 32 bits
+static_assert(CTX == 32, "a row is one word");
+
+struct CTileOut {
+  uint32_t word[kCRows];
+  uint16_t base[kCRows];
+  uint16_t root[kCRuns];
+};
+static_assert(sizeof(CTileOut) <= kCOwned * sizeof(uint16_t), "fits the slot");
+
+__device__ __forceinline__ CTileOut *ctile_out(uint16_t *loc, int64_t t) {
+  return reinterpret_cast<CTileOut *>(loc + t * kCOwned);
+}
+
+// First and last bits of a word's runs, and the number of the run that holds
+// bit x among them.
+__device__ __forceinline__ uint32_t run_starts(uint32_t w) {
+  return w & ~(w << 1);
+}
+__device__ __forceinline__ uint32_t run_ends(uint32_t w) {
+  return w & ~(w >> 1);
+}
+__device__ __forceinline__ uint32_t run_of(uint32_t starts, int x) {
+  return (uint32_t)__popc(starts & (0xffffffffu >> (31 - x))) - 1u;
 }
 
 // Global id of the tile-local index l (lx + CTX*(ly + CTY*lz)).
@@ -204,7 +228,7 @@ __device__ __forceinline__ int64_t ctile_global(const CGeo &g, const CTile &t,
 struct CGrid {
   const uint8_t *mask;
   int64_t *L;      // labels, also the union-find parent array
-  uint16_t *loc;   // tile-local roots (workspace), tile-major (loc_index)
+  uint16_t *loc;   // the tiles' slots (workspace): ctile_out
   int64_t off;     // added to every label (a slab inside a larger grid)
   int64_t X, Y, Z;
   uint32_t tile0;  // first tile of this mask in the launch
@@ -238,120 +262,134 @@ __device__ __forceinline__ const CGrid &cgrid_of(const CBatch<B> &b,
   return d;
 }
 
-// First z of the run of consecutive set bits of `bits` that contains bit z.
-__device__ __forceinline__ int run_start(uint32_t bits, int z) {
-  const uint32_t zeros = ~bits & ((1u << z) - 1u);
-  return zeros ? 32 - __clz(zeros) : 0;
+// 32 mask bytes from p as bits (any alignment; they must exist).
+__device__ __forceinline__ uint32_t mask_bits32(const uint8_t *p) {
+  struct __attribute__((packed)) Bytes {
+    uint32_t w[8];
+  };
+  const Bytes b = *reinterpret_cast<const Bytes *>(p);
+  uint32_t m = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    // The top bit of every byte that is not zero, then those four together.
+    const uint32_t t = (((b.w[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | b.w[k]) &
+                       0x80808080u;
+    m |= (((t >> 7) * 0x01020408u) >> 24) << (4 * k);
+  }
+  return m;
 }
 
+// One thread per row.  A row's runs of masked x are the nodes: joining them
+// settles every x edge, and the edges between two rows are joined once per
+// pair of runs that touch, found with a few operations on the rows' words,
+// whatever the number of vertices.  What bounds the pass is the latency of its
+// steps (load, scan, unions in LDS, stores), so a tile holds four waves and a
+// CU six tiles.  At 1024^3 with 30 % in the mask it takes 0.45 ms; with a
+// thread per column, which loads its bytes one by one and unites vertex by
+// vertex, it took 2.0.
+constexpr int kCTileThreads = kCRows;
+
 template <int B>
-__global__ void __launch_bounds__(kCThreads) k_cc_tile(CBatch<B> b) {
-  __shared__ int32_t par[kCOwned];
-  __shared__ uint32_t cols[kCThreads];  // mask bits of every column
-  const int tid = threadIdx.x;
+__global__ void __launch_bounds__(kCTileThreads) k_cc_tile(CBatch<B> b) {
+  __shared__ int32_t par[kCRuns];
+  __shared__ uint16_t head[kCRuns];        // local index of a run's first vertex
+  __shared__ uint32_t word[kCRows], base[kCRows];
+  __shared__ uint32_t wsum[kCTileThreads / 64];
+  const int r = threadIdx.x, lane = r & 63, wave = r >> 6;
   CGeo g;
   int64_t ti;
   const CGrid &d = cgrid_of(b, cc_tile_of_block(blockIdx.x, gridDim.x), &g,
                             &ti);
-  const uint8_t *__restrict__ mask = d.mask;
-  uint16_t *__restrict__ loc = d.loc;
-  int64_t *__restrict__ L = d.L;
   const CTile t = ctile_at(g, ti);
-  const int cx = tid % CTX, cy = tid / CTX;
-  const int64_t gx = t.x0 + cx, gy = t.y0 + cy;
-  const bool col_in = gx < g.X && gy < g.Y;
-  int nz = (int)((g.Z - t.z0) < CTZ ? (g.Z - t.z0) : CTZ);
-  if (!col_in) nz = 0;
-  const int64_t v0 = gx + g.X * gy + g.XY * t.z0;
-  auto local = [](int x, int y, int z) { return x + CTX * (y + CTY * z); };
-
-  // This column's mask bits.  The loads are unconditional, at addresses
-  // kept inside the mask (a plane past the column, or a column past the
-  // grid, reads a vertex that exists), so that all of them are in flight
-  // together; the planes past the column are then dropped.
+  const int ly = r % CTY, lz = r / CTY;
+  const int64_t gy = t.y0 + ly, gz = t.z0 + lz;
   uint32_t m = 0;
+  if (gy < g.Y && gz < g.Z) {
+    const int64_t at = t.x0 + g.X * gy + g.XY * gz;
+    const int nx = (int)(g.X - t.x0 < CTX ? g.X - t.x0 : CTX);
+    if (at + CTX <= g.N) {
+      m = mask_bits32(d.mask + at) & (0xffffffffu >> (CTX - nx));
+    } else {  // the mask's last rows: no byte past its end
+      for (int x = 0; x < nx; ++x) m |= (uint32_t)(d.mask[at + x] != 0) << x;
+    }
+  }
+  // Run numbers: an exclusive scan of the rows' counts.
+  const uint32_t st = run_starts(m), cnt = (uint32_t)__popc(st);
+  uint32_t inc = cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  word[r] = m;
+  __syncthreads();
+  uint32_t first = inc - cnt, runs = 0;
+#pragma unroll
+  for (int w = 0; w < kCTileThreads / 64; ++w) {
+    first += w < wave ? wsum[w] : 0u;
+    runs += wsum[w];
+  }
+  base[r] = first;
   {
-    const int64_t vb = col_in ? v0 : 0;
-    uint8_t mv[CTZ];
-#pragma unroll
-    for (int lz = 0; lz < CTZ; ++lz) mv[lz] = mask[vb + g.XY * (lz < nz ? lz : 0)];
-#pragma unroll
-    for (int lz = 0; lz < CTZ; ++lz) m |= (uint32_t)(lz < nz && mv[lz] != 0) << lz;
-  }
-  // The column's runs of consecutive masked z: every vertex of a run points
-  // at the run's first vertex, which settles every -z edge of the tile.
-#pragma unroll
-  for (int lz = 0; lz < CTZ; ++lz)
-    par[local(cx, cy, lz)] =
-        ((m >> lz) & 1u) ? local(cx, cy, run_start(m, lz)) : -1;
-  cols[tid] = m;
-  __syncthreads();
-
-  // The other lower-id Freudenthal edges of each masked vertex, united run
-  // head to run head.  The -x and -y edges are always taken; a diagonal one
-  // is implied, and skipped, when an axis neighbour on its side is in the
-  // mask: e.g. with v-x in the mask, v-x-y is v-x's own -y neighbour, so
-  // v ~ v-x ~ v-x-y (by induction on id, as v-x < v settles its own lower
-  // edges the same way; v ~ v-z through their run).  A lane skips a union of
-  // the same two heads as its previous one in that direction, so runs that
-  // lie side by side are united once.
-  const uint32_t mx_ = cx > 0 ? cols[tid - 1] : 0u;
-  const uint32_t my_ = cy > 0 ? cols[tid - CTX] : 0u;
-  const uint32_t mxy = cx > 0 && cy > 0 ? cols[tid - CTX - 1] : 0u;
-  uint32_t last[6] = {~0u, ~0u, ~0u, ~0u, ~0u, ~0u};
-  auto unite = [&](int dir, int hl, int hu) {
-    const uint32_t key = (uint32_t)hl | ((uint32_t)hu << 13);
-    if (key == last[dir]) return;
-    last[dir] = key;
-    uf_unite<int32_t>(par, hl, hu);
-  };
-#pragma unroll
-  for (int lz = 0; lz < CTZ; ++lz) {
-    if (!((m >> lz) & 1u)) continue;
-    const int hl = local(cx, cy, run_start(m, lz));
-    const bool mx = (mx_ >> lz) & 1u, my = (my_ >> lz) & 1u;
-    const bool mz = lz > 0 && ((m >> (lz - 1)) & 1u);
-    if (mx) unite(0, hl, local(cx - 1, cy, run_start(mx_, lz)));
-    if (my) unite(1, hl, local(cx, cy - 1, run_start(my_, lz)));
-    if (!mx && !my && ((mxy >> lz) & 1u))
-      unite(2, hl, local(cx - 1, cy - 1, run_start(mxy, lz)));
-    if (lz > 0 && !mz) {
-      if (!mx && ((mx_ >> (lz - 1)) & 1u))
-        unite(3, hl, local(cx - 1, cy, run_start(mx_, lz - 1)));
-      if (!my && ((my_ >> (lz - 1)) & 1u))
-        unite(4, hl, local(cx, cy - 1, run_start(my_, lz - 1)));
-      if (!mx && !my && ((mxy >> (lz - 1)) & 1u))
-        unite(5, hl, local(cx - 1, cy - 1, run_start(mxy, lz - 1)));
+    uint32_t i = first;
+    for (uint32_t s = st; s; s &= s - 1, ++i) {
+      par[i] = (int32_t)i;
+      head[i] = (uint16_t)(r * CTX + __ffs((int)s) - 1);
     }
   }
   __syncthreads();
-
-  // Tile-local roots, once per run.
-  int run_head = -1, run_root = -1;
-  for (int lz = 0; lz < nz; ++lz) {
-    const int64_t v = v0 + g.XY * lz;
-    const int l = local(cx, cy, lz);
-    if (!((m >> lz) & 1u)) {
-      loc[loc_index(ti, l)] = kOutside;
-      continue;
+  // Edges to the rows before (y-1), (z-1) and (y-1, z-1): x touches x and x-1
+  // there.  A run A = [a, b] and a run B = [c, e] of the other row touch when
+  // c <= b and e >= a - 1: they overlap from max(a, c) on, where one of them
+  // starts, or B ends just before a.  An edge into the diagonal row is implied
+  // where x is masked in one of the other two rows.
+  if (m) {
+    const uint32_t ny = ly > 0 ? word[r - 1] : 0u;
+    const uint32_t nz = lz > 0 ? word[r - CTY] : 0u;
+    const uint32_t nd = ly > 0 && lz > 0 ? word[r - CTY - 1] : 0u;
+    auto join = [&](uint32_t nw, int row, uint32_t skip) {
+      const uint32_t sn = run_starts(nw);
+      const uint32_t bn = base[row];
+      for (uint32_t c = m & nw & (st | sn) & ~skip; c; c &= c - 1) {
+        const int x = __ffs((int)c) - 1;
+        uf_unite<int32_t>(par, (int32_t)(first + run_of(st, x)),
+                          (int32_t)(bn + run_of(sn, x)));
+      }
+      for (uint32_t c = st & ~nw & (nw << 1) & ~skip; c; c &= c - 1) {
+        const int x = __ffs((int)c) - 1;  // at least 1
+        uf_unite<int32_t>(par, (int32_t)(first + run_of(st, x)),
+                          (int32_t)(bn + run_of(sn, x - 1)));
+      }
+    };
+    if (ny) join(ny, r - 1, 0u);
+    if (nz) join(nz, r - CTY, 0u);
+    if (nd) join(nd, r - CTY - 1, ny | nz);
+  }
+  __syncthreads();
+  CTileOut *out = ctile_out(d.loc, ti);
+  out->word[r] = m;
+  out->base[r] = (uint16_t)first;
+  for (uint32_t i = r; i < runs; i += kCTileThreads) {
+    const int32_t root = uf_find<int32_t>(par, (int32_t)i);
+    out->root[i] = head[root];
+    if (root == (int32_t)i) {  // tile-local roots start as global roots
+      const int64_t v = ctile_global(g, t, head[i]);
+      d.L[v] = v;
     }
-    const int h = local(cx, cy, run_start(m, lz));
-    if (h != run_head) {
-      run_head = h;
-      run_root = uf_find<int32_t>(par, h);
-    }
-    loc[loc_index(ti, l)] = (uint16_t)run_root;
-    if (run_root == l) L[v] = v;  // tile-local roots start as global roots
   }
 }
 
 // Unions across tile faces.  An edge between two tiles is handled by the tile
 // that owns its lower endpoint, which sees it as one of the 7 higher-id
-// neighbours leaving the tile through an upper face.  Both endpoints are
-// replaced by their tile-local roots, and each distinct (local root,
-// neighbour tile, its local root) triple is united once, after the block has
-// collected them: a face of a smooth mask carries thousands of edges but
-// only a few such triples.
+// neighbours leaving the tile through an upper face.  Both ends' runs are
+// replaced by their tile-local roots, and each distinct (local root, neighbour
+// tile, its local root) triple is united once, after the block has collected
+// them: a face of a smooth mask carries thousands of edges but only a few such
+// triples.  One thread per row, on the words of the tile's rows, of the rows
+// just beyond it, and of the tiles one up in x: 2.3 KB in a few whole lines,
+// where a 16-bit entry per vertex of the faces touched every line of the
+// workspace (1024^3: 0.33 ms instead of 2.1).
 constexpr int kCrossSlots = 2048;
 constexpr int kCrossProbes = 16;
 
@@ -386,101 +424,94 @@ __device__ __forceinline__ void cross_unite(const CGeo &g, const CTile &t,
 }
 
 template <int B>
-__global__ void __launch_bounds__(kCThreads) k_cc_cross(CBatch<B> b) {
+__global__ void __launch_bounds__(kCRows) k_cc_cross(CBatch<B> b) {
   static_assert(kCOwned <= (1 << 13), "13-bit local roots in the keys");
-  // The tile grown by one vertex on its upper sides; only the two upper
-  // layers of each side are read: the tile's upper faces and the vertices
-  // just beyond them.  Entries hold tile-local roots (kOutside: unmasked or
-  // outside the domain), decoded with their own tile's origin later.
-  constexpr int BX = CTX + 1, BY = CTY + 1, BZ = CTZ + 1, BXY = BX * BY;
-  constexpr int BN = BXY * BZ;
-  // The shell, in three disjoint slabs: bx >= CTX - 1 (all y, z); by >=
-  // CTY - 1 (bx below that); bz >= CTZ - 1 (bx and by below).
-  constexpr int S1 = 2 * BY * BZ, S2 = (CTX - 1) * 2 * BZ,
-                S3 = (CTX - 1) * (CTY - 1) * 2, SN = S1 + S2 + S3;
-  constexpr int K = (SN + kCThreads - 1) / kCThreads;
-  __shared__ uint16_t box[BN];
+  // Rows (ly, lz) of the tile and one beyond in y and z: their words and first
+  // run numbers in this x column of tiles, and in the next.
+  constexpr int SY = CTY + 1, SN = SY * (CTZ + 1);
+  __shared__ uint32_t w0[SN], wx[SN];
+  __shared__ uint16_t b0[SN], bx[SN];
   __shared__ uint32_t set[kCrossSlots];
-  const int tid = threadIdx.x;
-  for (int i = tid; i < kCrossSlots; i += kCThreads) set[i] = kNoKey;
+  const int r = threadIdx.x;
+  for (int i = r; i < kCrossSlots; i += kCRows) set[i] = kNoKey;
   CGeo g;
   int64_t ti;
   const CGrid &d = cgrid_of(b, cc_tile_of_block(blockIdx.x, gridDim.x), &g,
                             &ti);
-  const uint16_t *__restrict__ loc = d.loc;
   int64_t *L = d.L;
   const CTile t = ctile_at(g, ti);
-  {
-    uint16_t val[K];
-    int at[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = tid + k * kCThreads;
-      int bx, by, bz;
-      if (i < S1) {
-        bz = i / (2 * BY);
-        const int r = i - bz * (2 * BY);
-        by = r >> 1;
-        bx = CTX - 1 + (r & 1);
-      } else if (i < S1 + S2) {
-        const int j = i - S1;
-        bz = j / (2 * (CTX - 1));
-        const int r = j - bz * (2 * (CTX - 1));
-        by = CTY - 1 + r / (CTX - 1);
-        bx = r % (CTX - 1);
-      } else {
-        const int j = i - S1 - S2;
-        bz = CTZ - 1 + j / ((CTX - 1) * (CTY - 1));
-        const int r = j % ((CTX - 1) * (CTY - 1));
-        by = r / (CTX - 1);
-        bx = r % (CTX - 1);
-      }
-      const int64_t x = t.x0 + bx, y = t.y0 + by, z = t.z0 + bz;
-      const bool in = i < SN && x < g.X && y < g.Y && z < g.Z;
-      at[k] = i < SN ? bx + BX * (by + BY * bz) : -1;
-      const int64_t tn = x / CTX + g.ntx * (y / CTY + g.nty * (z / CTZ));
-      const int ln = (int)(x % CTX) + CTX * ((int)(y % CTY) + CTY * (int)(z % CTZ));
-      val[k] = in ? loc[loc_index(tn, ln)] : kOutside;
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-      if (at[k] >= 0) box[at[k]] = val[k];
+  const bool ux = t.x0 + CTX < g.X, uy = t.y0 + CTY < g.Y,
+             uz = t.z0 + CTZ < g.Z;
+  for (int i = r; i < SN; i += kCRows) {
+    const int yy = i % SY, zz = i / SY;
+    const bool oy = yy == CTY, oz = zz == CTZ;
+    const bool in = (!oy || uy) && (!oz || uz);
+    const int row = (oy ? 0 : yy) + CTY * (oz ? 0 : zz);
+    const int64_t tn = in ? ti + (oy ? g.ntx : 0) + (oz ? g.ntx * g.nty : 0)
+                          : ti;
+    const CTileOut *o = ctile_out(d.loc, tn), *ox = ctile_out(d.loc, ux ? tn + 1 : tn);
+    const uint32_t a = o->word[row], c = ox->word[row];
+    const uint16_t ab = o->base[row], cb = ox->base[row];
+    w0[i] = in ? a : 0u;
+    b0[i] = ab;
+    wx[i] = in && ux ? c : 0u;
+    bx[i] = cb;
   }
   __syncthreads();
-  // Every masked vertex on an upper face, with each of its higher-id
-  // Freudenthal neighbours that lies beyond the face (and in the mask).
-  const int cx = tid % CTX, cy = tid / CTX;
-  const bool xface = cx == CTX - 1, yface = cy == CTY - 1;
-  uint32_t last = kNoKey;
-  for (int lz = 0; lz < CTZ; ++lz) {
-    const bool zface = lz == CTZ - 1;
-    if (!(xface || yface || zface)) continue;
-    const int bv = cx + BX * (cy + BY * lz);
-    const uint32_t lv = box[bv];
-    if (lv == kOutside) continue;
-    const int dx[7] = {1, 0, 1, 0, 1, 0, 1};
-    const int dy[7] = {0, 1, 1, 0, 0, 1, 1};
-    const int dz[7] = {0, 0, 0, 1, 1, 1, 1};
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-      const bool leaves = (dx[k] && xface) || (dy[k] && yface) ||
-                          (dz[k] && zface);
-      if (!leaves) continue;
-      const uint32_t lu = box[bv + dx[k] + BX * (dy[k] + BY * dz[k])];
-      if (lu == kOutside) continue;
-      // Which neighbour tile u lies in: one up along each axis it crossed.
-      const uint32_t nbr = (uint32_t)(dx[k] && xface) |
-                           ((uint32_t)(dy[k] && yface) << 1) |
-                           ((uint32_t)(dz[k] && zface) << 2);
+  const int y = r % CTY, z = r / CTY;
+  const int i0 = y + SY * z, iy = i0 + 1, iz = i0 + SY, id = i0 + SY + 1;
+  const uint32_t m = w0[i0];
+  if (m) {
+    const uint32_t st = run_starts(m), en = run_ends(m);
+    const uint16_t *own = ctile_out(d.loc, ti)->root;
+    const uint32_t nyr = y == CTY - 1 ? 2u : 0u, nzr = z == CTZ - 1 ? 4u : 0u;
+    uint32_t last = kNoKey;
+    // The run of x in this row with run k of the tile one up along `nbr`.
+    auto pair = [&](int x, uint32_t nbr, uint32_t k) {
+      const int64_t tn = ti + (nbr & 1u ? 1 : 0) + (nbr & 2u ? g.ntx : 0) +
+                         (nbr & 4u ? g.ntx * g.nty : 0);
+      const uint32_t lv = own[b0[i0] + run_of(st, x)];
+      const uint32_t lu = ctile_out(d.loc, tn)->root[k];
       const uint32_t key = lv | (nbr << 13) | (lu << 16);
-      if (key == last) continue;  // a lane's edges mostly repeat their roots
+      if (key == last) return;  // a row's edges mostly repeat their roots
       last = key;
       if (!cross_insert(set, key)) cross_unite(g, t, key, L);
+    };
+    // Edges into row i of the tile up along `nbr`: x touches x and x+1 there,
+    // so a run A = [a, b] touches B = [c, e] when they overlap (from max(a, c)
+    // on) or c = b + 1.  `skip`: positions whose edges are implied.
+    auto rows = [&](int i, uint32_t nbr, uint32_t skip) {
+      const uint32_t nw = w0[i], sn = run_starts(nw);
+      for (uint32_t c = m & nw & (st | sn) & ~skip; c; c &= c - 1) {
+        const int x = __ffs((int)c) - 1;
+        pair(x, nbr, b0[i] + run_of(sn, x));
+      }
+      for (uint32_t c = en & ~nw & (nw >> 1) & ~skip; c; c &= c - 1) {
+        const int x = __ffs((int)c) - 1;  // at most CTX - 2
+        pair(x, nbr, b0[i] + run_of(sn, x + 1));
+      }
+    };
+    const uint32_t wy = w0[iy], wz = w0[iz];
+    if (nyr) rows(iy, nyr, 0u);
+    if (nzr) rows(iz, nzr, 0u);
+    // An edge into the diagonal row is implied where x is masked in one of the
+    // rows between.
+    if (nyr | nzr) rows(id, nyr | nzr, wy | wz);
+    // From the row's last vertex into the next tile in x: along x always; into
+    // another row only when neither end has a masked neighbour on the way.
+    constexpr int XL = CTX - 1;
+    if (m >> XL) {
+      const bool x0 = wx[i0] & 1u, xy = wx[iy] & 1u, xz = wx[iz] & 1u;
+      if (x0) pair(XL, 1u, bx[i0]);
+      if (xy && !x0 && !(wy >> XL)) pair(XL, 1u | nyr, bx[iy]);
+      if (xz && !x0 && !(wz >> XL)) pair(XL, 1u | nzr, bx[iz]);
+      if ((wx[id] & 1u) && !x0 && !xy && !xz && !((wy | wz | w0[id]) >> XL))
+        pair(XL, 1u | nyr | nzr, bx[id]);
     }
   }
   // Each distinct triple once, spread over the block.
   __syncthreads();
-  for (int i = tid; i < kCrossSlots; i += kCThreads) {
+  for (int i = r; i < kCrossSlots; i += kCRows) {
     const uint32_t key = set[i];
     if (key != kNoKey) cross_unite(g, t, key, L);
   }
@@ -490,67 +521,70 @@ __global__ void __launch_bounds__(kCThreads) k_cc_cross(CBatch<B> b) {
 // grid writes global ids).  The tile-local roots keep the unshifted root
 // here, since concurrent walks read their entries as indices; k_cc_root_shift
 // adds the offset to them afterwards.
+// Each run's label is looked up once, into LDS; a vertex then needs its row's
+// word and one LDS read.  Bound by the 8 bytes a vertex that are written
+// (1024^3: 1.60 ms, 5.4 TB/s; 2.25 with a 16-bit root read for every vertex).
 template <int B>
 __global__ void __launch_bounds__(kCThreads) k_cc_final(CBatch<B> b) {
+  __shared__ int64_t res[kCRuns];
+  __shared__ uint32_t word[kCRows], base[kCRows];
   const int tid = threadIdx.x;
   CGeo g;
   int64_t ti;
   const CGrid &d = cgrid_of(b, cc_tile_of_block(blockIdx.x, gridDim.x), &g,
                             &ti);
-  const uint16_t *__restrict__ loc = d.loc;
   int64_t *L = d.L;
   const int64_t off = d.off;
   const CTile t = ctile_at(g, ti);
+  const CTileOut *o = ctile_out(d.loc, ti);
+  if (tid < kCRows) {
+    word[tid] = o->word[tid];
+    base[tid] = o->base[tid];
+  }
+  __syncthreads();
+  const uint32_t runs =
+      base[kCRows - 1] + (uint32_t)__popc(run_starts(word[kCRows - 1]));
+  // Only tile-local roots are ever on a root path, and a root's entry is
+  // overwritten (by its owner only) with its own final root, so concurrent
+  // walks stay on ancestors and every entry ends as its final root.
+  for (uint32_t i = tid; i < runs; i += kCThreads)
+    res[i] = uf_root<int64_t>(L, ctile_global(g, t, o->root[i]));
+  __syncthreads();
   const int cx = tid % CTX, cy = tid / CTX;
   const int64_t gx = t.x0 + cx, gy = t.y0 + cy;
   if (gx >= g.X || gy >= g.Y) return;
   const int nz = (int)((g.Z - t.z0) < CTZ ? (g.Z - t.z0) : CTZ);
-  const int64_t v0 = gx + g.X * gy + g.XY * t.z0;
-  // The column's tile-local roots, all loads in flight together (entries
-  // past the domain's last plane exist in the tile's run and are not used).
-  uint16_t sl[CTZ];
-#pragma unroll
-  for (int lz = 0; lz < CTZ; ++lz)
-    sl[lz] = loc[loc_index(ti, tid + kCThreads * lz)];
-  uint16_t last = kOutside;
-  int64_t last_out = -1;
+  int64_t *const col = L + (gx + g.X * gy + g.XY * t.z0);
+#pragma unroll 4
   for (int lz = 0; lz < nz; ++lz) {
-    const uint16_t s = sl[lz];
-    // Only tile-local roots are ever on a root path, and a root's entry is
-    // overwritten (by its owner only) with its own final root, so concurrent
-    // walks stay on ancestors and every entry ends as its final root.  A
-    // column mostly repeats its local root: its final root is reused.
-    if (s != last && s != kOutside) {
-      last = s;
-      last_out = uf_root<int64_t>(L, ctile_global(g, t, s));
+    const int row = cy + CTY * lz;
+    const uint32_t w = word[row], st = run_starts(w);
+    int64_t v = -1;
+    if ((w >> cx) & 1u) {
+      const uint32_t k = base[row] + run_of(st, cx);
+      v = res[k];
+      // (a block-uniform test first)
+      if (off && o->root[k] != row * CTX + cx) v += off;
     }
-    const bool root = s == cx + CTX * (cy + CTY * lz);
-    __atomic_store_n(&L[v0 + g.XY * lz],
-                     s == kOutside ? -1 : last_out + (root ? 0 : off),
-                     __ATOMIC_RELAXED);
+    __hip_atomic_store(col + g.XY * lz, v, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 // The tile-local roots' labels take the offset once no walk is in flight.
 template <int B>
-__global__ void __launch_bounds__(kCThreads) k_cc_root_shift(CBatch<B> b) {
-  const int tid = threadIdx.x;
+__global__ void __launch_bounds__(kCRows) k_cc_root_shift(CBatch<B> b) {
+  const int r = threadIdx.x;
   CGeo g;
   int64_t ti;
   const CGrid &d = cgrid_of(b, cc_tile_of_block(blockIdx.x, gridDim.x), &g,
                             &ti);
-  const uint16_t *__restrict__ loc = d.loc;
-  int64_t *L = d.L;
-  const int64_t off = d.off;
   const CTile t = ctile_at(g, ti);
-  const int cx = tid % CTX, cy = tid / CTX;
-  const int64_t gx = t.x0 + cx, gy = t.y0 + cy;
-  if (gx >= g.X || gy >= g.Y) return;
-  int nz = (int)((g.Z - t.z0) < CTZ ? (g.Z - t.z0) : CTZ);
-  for (int lz = 0; lz < nz; ++lz) {
-    const int64_t v = gx + g.X * gy + g.XY * (t.z0 + lz);
-    const int l = cx + CTX * (cy + CTY * lz);
-    if (loc[loc_index(ti, l)] == l) L[v] += off;
+  const CTileOut *o = ctile_out(d.loc, ti);
+  uint32_t i = o->base[r];
+  for (uint32_t s = run_starts(o->word[r]); s; s &= s - 1, ++i) {
+    const int l = r * CTX + __ffs((int)s) - 1;
+    if (o->root[i] == l) d.L[ctile_global(g, t, l)] += d.off;
   }
 }
 
@@ -969,14 +1003,14 @@ template <int B>
 int cc_launch(msc_ctx *ctx, const CBatch<B> &b, uint32_t nb, int64_t nverts,
               bool shift, hipStream_t s) {
   MSC_PHASE(ctx, s, "cc_tile", 3.0 * nverts,
-            (k_cc_tile<B><<<nb, kCThreads, 0, s>>>(b)));
+            (k_cc_tile<B><<<nb, kCTileThreads, 0, s>>>(b)));
   MSC_PHASE(ctx, s, "cc_cross", 0.5 * nverts,
-            (k_cc_cross<B><<<nb, kCThreads, 0, s>>>(b)));
+            (k_cc_cross<B><<<nb, kCRows, 0, s>>>(b)));
   MSC_PHASE(ctx, s, "cc_final", 10.0 * nverts,
             (k_cc_final<B><<<nb, kCThreads, 0, s>>>(b)));
   if (shift)
     MSC_PHASE(ctx, s, "cc_root_shift", 2.0 * nverts,
-              (k_cc_root_shift<B><<<nb, kCThreads, 0, s>>>(b)));
+              (k_cc_root_shift<B><<<nb, kCRows, 0, s>>>(b)));
   return MSC_OK;
 }
 
@@ -1227,10 +1261,10 @@ extern "C" int cc_label_grid_noalloc(const uint8_t *mask,
   const unsigned nb = (unsigned)cc_tiles(X, Y, Z);
   const CBatch<1> b{1, {CGrid{mask, labels, loc, 0, X, Y, Z, 0u}}};
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Every entry of `loc` the kernels read is written first (k_cc_tile
-  // writes each vertex's root or kOutside), so nothing is cleared.
-  k_cc_tile<1><<<nb, kCThreads, 0, s>>>(b);
-  k_cc_cross<1><<<nb, kCThreads, 0, s>>>(b);
+  // Everything of a tile's slot that the kernels read k_cc_tile writes first
+  // (all rows, and the runs that they hold), so nothing is cleared.
+  k_cc_tile<1><<<nb, kCTileThreads, 0, s>>>(b);
+  k_cc_cross<1><<<nb, kCRows, 0, s>>>(b);
   k_cc_final<1><<<nb, kCThreads, 0, s>>>(b);
   return hipGetLastError() == hipSuccess ? MSC_OK : MSC_EHIP;
 }

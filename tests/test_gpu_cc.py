@@ -256,3 +256,42 @@ def test_csr_sizes(msc, n, deg, both):
         with pytest.raises(msc.MscError) as e:
             gpu_cc_csr(msc, row_ptr, col)
         assert e.value.code == msc.MSC_EINVAL
+
+
+@pytest.mark.parametrize("dims", [(31, 17, 16), (32, 16, 17), (33, 15, 33),
+                                  (64, 33, 16), (65, 32, 18), (97, 1, 1),
+                                  (1, 40, 35), (2, 18, 34), (130, 50, 1)])
+@pytest.mark.parametrize("kind", [0.1, 0.35, 0.6, 0.95, "comb", "full"])
+def test_rows_and_runs(msc, dims, kind):
+    """Around the 32 x 16 x 16 of a tile: masks of every density, the most runs
+    a row can hold, and a full one, at a byte address of no alignment; also
+    through the entry point without a context and through slabs."""
+    X, Y, Z = dims
+    rng = np.random.default_rng(sum(dims))
+    if kind == "comb":
+        x, y, z = np.meshgrid(np.arange(X), np.arange(Y), np.arange(Z),
+                              indexing="ij")
+        mask = ((x + 3 * y + 5 * z) % 2 == 0).transpose(2, 1, 0)
+        mask = mask & (rng.uniform(size=mask.shape) < 0.98)
+    elif kind == "full":
+        mask = np.ones((Z, Y, X), bool)
+    else:
+        mask = rng.uniform(size=(Z, Y, X)) < kind
+    # any non-zero byte is a feature
+    mask = mask.astype(np.uint8) * rng.choice([1, 2, 128, 255], size=mask.shape
+                                              ).astype(np.uint8)
+    want, _ = O.cc_grid(mask)
+    for shift in (0, 1, 7):
+        buf = torch.empty(mask.size + shift, dtype=torch.uint8, device="cuda")
+        part = buf[shift:]
+        part.copy_(torch.from_numpy(mask.reshape(-1)))
+        lab = torch.empty(mask.size, dtype=torch.int64, device="cuda")
+        msc.cc_label_grid_into(part, lab, dims=dims)
+        np.testing.assert_array_equal(lab.cpu().numpy(), want, err_msg=str(shift))
+    lab.zero_()
+    msc.cc_label_grid_noalloc_into(part, lab, dims=dims)
+    np.testing.assert_array_equal(lab.cpu().numpy(), want, err_msg="noalloc")
+    for ranks in {1, min(2, Z), min(5, Z)}:
+        got = msc.cc_label_grid_ranks(part, ranks, dims=dims)
+        np.testing.assert_array_equal(got.cpu().numpy(), want,
+                                      err_msg=f"{ranks} ranks")
