@@ -1569,6 +1569,21 @@ constexpr unsigned kCellIdx = 255;
 // 37 % on Perlin noise (512^3: 1.67 ms against 2.29 with every tile in slabs).
 constexpr unsigned kPairExtrema = 96;
 
+// A field alone in its call, of at most kAloneTiles tiles, with more extrema
+// than this per tile on average goes to the slab pass whole, its smooth tiles
+// too: the slowest tile of the pair pass then delays nothing (200^3 Gaussian
+// sums, mostly noise: 331 us with both passes, 310 so; 223x157x101: 171 and
+// 149; Perlin noise, 13 a tile, would take 198 us instead of 164).  At 260^3
+// (2,601 tiles) it costs 2 %, and in batches, where some fields are smooth,
+// 3 %.
+constexpr unsigned kNoisyField = 48;
+constexpr uint32_t kAloneTiles = 2048;
+
+// And calls of at most this many tiles leave the pair pass out, which is a
+// launch more (64^3: 110 -> 92 us, 100x90x80 Perlin 72 -> 69; at 500 tiles
+// Perlin noise loses, 101 -> 112).
+constexpr uint32_t kSlabOnlyTiles = 256;
+
 template <class C>
 __device__ __forceinline__ uint32_t *cell_record(uint16_t *tlist,
                                                  uint32_t gt) {
@@ -1598,7 +1613,7 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, unsigned long long *ctr,
              uint32_t *tstat, uint16_t *tlist, uint32_t *cidx,
-             unsigned long long *dcells) {
+             const unsigned long long *alone, unsigned long long *dcells) {
   static_assert(C::TZ % 4 == 0, "four planes per index word");
   __shared__ Decode<C> s;
   __shared__ uint32_t s_fresh[C::kThreads / 64];
@@ -1615,7 +1630,9 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
   const unsigned inside = min(C::TX, (int)g.X - t.x0) *
                           min(C::TY, (int)g.Y - t.y0) *
                           min(C::TZ, (int)g.Z - t.z0);
-  if (ts[0] + ts[1] > kPairExtrema && inside > kPairLimit) {
+  if ((ts[0] + ts[1] > kPairExtrema && inside > kPairLimit) ||
+      (alone && alone[kFMaxima] + alone[kFMinima] >
+                    (unsigned long long)kNoisyField * g.ntiles)) {
     if (tid == 0) ts[2] = kTilePending;  // uniform over the block
     return;
   }
@@ -1780,11 +1797,12 @@ k_tile_slabs(const FieldDev *__restrict__ fds,
   __shared__ uint32_t s_fresh;
   const int tid = threadIdx.x;
   if (again && !(ctr[kCtrOverflow] & kOverflowFirst)) return;
+  const bool all = again || ntiles <= kSlabOnlyTiles;
   const uint64_t units = (uint64_t)ntiles * NS;  // slabs of all tiles
   for (uint64_t u0 = blockIdx.x; u0 < units; u0 += 64ull * gridDim.x) {
     const uint64_t ul = u0 + (uint64_t)(tid & 63) * gridDim.x;
     unsigned long long todo = __ballot(
-        ul < units && (again || (tstat[4 * (ul / NS) + 2] & kTilePending)));
+        ul < units && (all || (tstat[4 * (ul / NS) + 2] & kTilePending)));
     for (; todo; todo &= todo - 1) {
       const uint64_t u =
           u0 + (uint64_t)(__ffsll((long long)todo) - 1) * gridDim.x;
@@ -2398,9 +2416,12 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
     // table runs once more on the capacity that always suffices (the second
     // pass and its clear return at once when nothing overflowed).
     unsigned long long *const dcells = direct ? fctr + kFCells : nullptr;
-    MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
-              (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
-                  fds, tfield, seg, next, ctr, tstat, tlist, cidx, dcells)));
+    if (nt > kSlabOnlyTiles)
+      MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
+                (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
+                    fds, tfield, seg, next, ctr, tstat, tlist, cidx,
+                    nfields == 1 && nt <= kAloneTiles ? fctr : nullptr,
+                    dcells)));
     const unsigned sb =
         std::min<uint64_t>((uint64_t)nt * (C::TZ / kSlabZ), kSlabBlocks);
     MSC_PHASE(ctx, s, "tile_slabs", 0.0,

@@ -318,3 +318,21 @@ def test_cell_passes(msc, dims, kind):
     finally:
         msc.set_table_capacity(0)
         msc.set_tile(*msc.tile_shapes()[0])
+
+
+@pytest.mark.parametrize("dims", [(512, 256, 1), (512, 257, 1), (128, 128, 65),
+                                  (160, 160, 40)])
+@pytest.mark.parametrize("kind", ["noise", "half", 0.1])
+def test_cell_passes_by_call_size(msc, dims, kind):
+    """Calls of 256 tiles (slabs only) and just above, with fields that go to
+    the slab pass whole, in part, and not at all."""
+    if kind == 0.1:
+        f = synth.perlin_field(dims, seed=5, frequency=kind)
+    else:
+        f = synth.random_field(dims, seed=5)
+        if kind == "half":
+            f[:, : f.shape[1] * 9 // 10] = synth.perlin_field(
+                dims, seed=5)[:, : f.shape[1] * 9 // 10]
+    assert_parity(msc, f, f"{dims} {kind}")
+    st = msc.last_stats()
+    assert st["n_cells"] == np.unique(O.segment(f)[2]).size
