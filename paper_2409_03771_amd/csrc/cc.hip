@@ -1960,14 +1960,15 @@ __device__ __forceinline__ uint32_t component_extremes(uint32_t set,
 // vertices of a plane are 64 consecutive ids (a run).  What bounds these passes
 // is vector and LDS issue, about 50 vector operations a vertex (189 with
 // fifteen loads and a vertex's own coordinates).  Critical points of 512^3 take
-// 0.28 ms instead of 0.60 (2.4 TB/s of the 5 bytes a vertex), 0.35 without the
-// load ahead.
+// 0.26 ms instead of 0.60 (2.6 TB/s of the 5 bytes a vertex); 0.28 rolled, 0.35
+// without the load ahead.
 constexpr int kWalkThreads = 512;
 
 struct Walk {
   const float *f;
   uint32_t X, Y, Z, XY, runs;  // runs of 64 positions per plane
-  uint32_t pb, zc;             // blocks per plane, planes per walk
+  uint32_t pb;                 // blocks per plane
+  int zc;                      // planes per walk
 };
 
 // idx * 2 + (the lane's bit of m).
@@ -1981,9 +1982,11 @@ __device__ __forceinline__ unsigned long long lanes(bool b) {
   return __builtin_amdgcn_ballot_w64(b);
 }
 
-// Calls use(z, p, inside, lower, upper) for every plane of the block's chunk,
-// with all lanes; returns whether a value of the lane's was NaN.
-template <class Use>
+// Calls use(z, p, inside, lower, upper) for every plane of the block's chunk of
+// ZC planes, with all lanes; returns whether a value of the lane's was NaN.
+// The walk is unrolled, so that the planes' registers change their names and
+// are not copied (18 of 75 operations a vertex).
+template <int ZC, class Use>
 __device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
   const uint32_t blk = cc_tile_of_block(blockIdx.x, gridDim.x);
   const uint32_t chunk = blk / w.pb;
@@ -2020,8 +2023,7 @@ __device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
     GF *q = plane(z);
     return PlaneH{q[oxh], q[oyh], q[oxyh]};
   };
-  const uint32_t z0 = chunk * w.zc;
-  const uint32_t z1 = z0 + w.zc < w.Z ? z0 + w.zc : w.Z;
+  const uint32_t z0 = chunk * ZC;
   // The plane above is loaded one step ahead of its use.
   auto in_z = [&](uint32_t z) { return z < w.Z ? z : w.Z - 1; };
   PlaneL below = load_l(z0 > 0 ? z0 - 1 : 0), cur = load_l(z0);
@@ -2029,7 +2031,10 @@ __device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
   PlaneL up = load_l(in_z(z0 + 1));
   PlaneH uph = load_h(in_z(z0 + 1));
   bool nan = false;
-  for (uint32_t z = z0; z < z1; ++z) {
+#pragma unroll
+  for (uint32_t k = 0; k < (uint32_t)ZC; ++k) {
+    const uint32_t z = z0 + k;
+    if (z >= w.Z) break;  // uniform
     const PlaneL next = load_l(in_z(z + 2));
     const PlaneH nexth = load_h(in_z(z + 2));
     const float v = cur.c;
@@ -2072,12 +2077,13 @@ __device__ __forceinline__ void stage_ncomp(uint8_t *t) {
   __syncthreads();
 }
 
+template <int ZC>
 __global__ void __launch_bounds__(kWalkThreads)
 k_critical(Walk w, uint8_t *__restrict__ code, unsigned long long *ctr) {
   __shared__ __align__(16) uint8_t nc[kLinkSets];
   stage_ncomp(nc);
   typedef __attribute__((address_space(1))) uint8_t GB;
-  const bool nan = walk_links(w, [&](uint32_t z, uint32_t p, bool inside,
+  const bool nan = walk_links<ZC>(w, [&](uint32_t z, uint32_t p, bool inside,
                                      uint32_t lower, uint32_t upper) {
     const uint32_t c = nc[lower] | (uint32_t)nc[upper] << 4;
     if (inside) ((GB *)code + (size_t)w.XY * z)[p] = (uint8_t)c;
@@ -2151,12 +2157,13 @@ __device__ __forceinline__ void egraph_emit(const LinkSets &ls, int64_t v,
 
 // Every run's vertices with edges as a lane mask, and the number of the run's
 // edges; the write pass then looks at those vertices alone.
+template <int ZC>
 __global__ void __launch_bounds__(kWalkThreads)
 k_egraph_mark(Walk w, unsigned long long *__restrict__ marks,
               uint32_t *__restrict__ counts, unsigned long long *ctr) {
   __shared__ __align__(16) uint8_t nc[kLinkSets];
   stage_ncomp(nc);
-  const bool nan = walk_links(w, [&](uint32_t z, uint32_t p, bool inside,
+  const bool nan = walk_links<ZC>(w, [&](uint32_t z, uint32_t p, bool inside,
                                      uint32_t lower, uint32_t upper) {
     const uint32_t c = inside ? edge_count(nc[lower], nc[upper]) : 0u;
     const unsigned long long m = lanes(c != 0u);
@@ -2283,7 +2290,7 @@ k_egraph_write_small(const float *__restrict__ f, int64_t X, int64_t Y,
 }
 
 // Planes per walk: 16 share the two extra planes and the staged table well;
-// fewer where the grid would not give each CU four blocks.
+// four where the grid would not give each CU four blocks.
 Walk make_walk(const float *f, const int64_t *dims, unsigned *blocks) {
   Walk w;
   w.f = f;
@@ -2293,9 +2300,8 @@ Walk make_walk(const float *f, const int64_t *dims, unsigned *blocks) {
   w.XY = w.X * w.Y;
   w.runs = (w.XY + 63) / 64;
   w.pb = (w.XY + kWalkThreads - 1) / kWalkThreads;
-  w.zc = 16;
-  while (w.zc > 2 && (uint64_t)w.pb * ((w.Z + w.zc - 1) / w.zc) < 1024)
-    w.zc /= 2;
+  const uint64_t big = (uint64_t)w.pb * ((w.Z + 15) / 16);
+  w.zc = big >= 1024 ? 16 : 4;
   *blocks = w.pb * ((w.Z + w.zc - 1) / w.zc);
   return w;
 }
@@ -2309,7 +2315,10 @@ int critical_points_run(msc_ctx *ctx, const float *field, const int64_t *dims,
   const Walk w = make_walk(field, dims, &nb);
   MSC_TRY(clear_counters(ctx, s));
   MSC_PHASE(ctx, s, "critical", 5.0 * N,
-            (k_critical<<<nb, kWalkThreads, 0, s>>>(w, code, ctx->dctr)));
+            (w.zc == 16
+                 ? k_critical<16><<<nb, kWalkThreads, 0, s>>>(w, code, ctx->dctr)
+                 : k_critical<4><<<nb, kWalkThreads, 0, s>>>(w, code,
+                                                             ctx->dctr)));
   MSC_TRY(read_counters(ctx, s));
   if (ctx->hctr[kCtrNaN]) return MSC_ENAN;
   ctx->stats = msc_stats{};
@@ -2344,9 +2353,12 @@ int extremum_graph_run(msc_ctx *ctx, const float *field, const int64_t *dims,
   MSC_TRY(clear_counters(ctx, s));
   MSC_PHASE(
       ctx, s, "egraph_count", 4.0 * N,
-      (marked ? k_egraph_mark<<<wb, kWalkThreads, 0, s>>>(w, marks, cnt,
-                                                          ctx->dctr)
-              : k_egraph_count_small<<<(unsigned)nb, kBlock, 0, s>>>(
+      (marked && w.zc == 16
+           ? k_egraph_mark<16><<<wb, kWalkThreads, 0, s>>>(w, marks, cnt,
+                                                           ctx->dctr)
+       : marked ? k_egraph_mark<4><<<wb, kWalkThreads, 0, s>>>(w, marks, cnt,
+                                                               ctx->dctr)
+                : k_egraph_count_small<<<(unsigned)nb, kBlock, 0, s>>>(
                     field, X, Y, Z, cnt, ctx->dctr),
        scan64(ctx, cnt, nc, off, bsum, s)));
   MSC_TRY(read_counters(ctx, s, off + nc));
