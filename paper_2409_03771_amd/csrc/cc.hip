@@ -610,8 +610,8 @@ __global__ void __launch_bounds__(kCRows) k_cc_root_shift(CBatch<B> b) {
 //    goes on only where a bit is clear.
 // Every edge of every row is still examined, so rows that list an edge in one
 // direction only are as good as symmetric ones.  50M vertices with 30 % in the
-// mask take 7.0 ms instead of 14.2 (the union pass 2.6 instead of 8.9, the
-// hooks 1.1 instead of 3.9, the joins 1.5), 1M vertices without a mask 0.25
+// mask take 6.3 ms instead of 14.2 (the union pass 2.6 instead of 8.9, the
+// hooks 1.1 instead of 3.9, the joins 0.8), 1M vertices without a mask 0.25
 // instead of 0.73.
 
 // Edges of a CSR row handled together, so that their gathers overlap.
@@ -1099,8 +1099,11 @@ constexpr int64_t kCsrLarge = 1 << 12;
 // and larger from round to round, so fewer attempts reach all of them.  With
 // every vertex in each of four rounds 50M vertices take 8.4 ms instead of 7.1,
 // 1M take 0.29 instead of 0.25; with two rounds too many trees are left and
-// 1M take 1.7 ms.
+// 1M take 1.7 ms.  Half as many attempts in every round do from kJoinHalf
+// vertices on (50M: 7.0 -> 6.3 ms, 8M: 1.44 -> 1.31; 1M: 0.25 and 0.26, and
+// 8,000 take 108 us instead of 83).
 constexpr int kJoinStride[] = {1, 4, 16, 32};
+constexpr int64_t kJoinHalf = 1 << 21;
 constexpr int kJoins = sizeof(kJoinStride) / sizeof(int);
 
 int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
@@ -1127,10 +1130,11 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
             (k_csr_compress<<<nb, kBlock, 0, s>>>(n, P)));
   if (large) {
     for (int k = 0; k < kJoins; ++k) {
-      const int64_t waves = (n + 64 * kJoinStride[k] - 1) / (64 * kJoinStride[k]);
+      const int stride = kJoinStride[k] * (n >= kJoinHalf ? 2 : 1);
+      const int64_t waves = (n + 64 * stride - 1) / (64 * stride);
       MSC_PHASE(ctx, s, "csr_join", 21.0 * n,
-                (k_csr_join<<<grid_for(64 * waves), kBlock, 0, s>>>(
-                    g, P, kJoinStride[k], k)));
+                (k_csr_join<<<grid_for(64 * waves), kBlock, 0, s>>>(g, P,
+                                                                    stride, k)));
       if (k == 0) k_csr_compress<<<nb, kBlock, 0, s>>>(n, P);
     }
     k_csr_compress<<<nb, kBlock, 0, s>>>(n, P);
