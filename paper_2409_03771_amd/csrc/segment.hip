@@ -1569,15 +1569,16 @@ constexpr unsigned kCellIdx = 255;
 // 37 % on Perlin noise (512^3: 1.67 ms against 2.29 with every tile in slabs).
 constexpr unsigned kPairExtrema = 96;
 
-// A field alone in its call, of at most kAloneTiles tiles, with more extrema
-// than this per tile on average goes to the slab pass whole, its smooth tiles
-// too: the slowest tile of the pair pass then delays nothing (200^3 Gaussian
-// sums, mostly noise: 331 us with both passes, 310 so; 223x157x101: 171 and
-// 149; Perlin noise, 13 a tile, would take 198 us instead of 164).  At 260^3
-// (2,601 tiles) it costs 2 %, and in batches, where some fields are smooth,
-// 3 %.
+// A call of few tiles with more extrema than this per tile on average goes to
+// the slab pass whole, its smooth tiles too: the slowest tile of the pair pass
+// then delays nothing (200^3 Gaussian sums, mostly noise: 331 us with both
+// passes, 310 so; 223x157x101: 171 and 149; a captured batch of four 152 and
+// 136; Perlin noise, 13 a tile, would take 198 us instead of 164).  Few are
+// 2,048 tiles of one field (260^3, 2,601 tiles, loses 2 %) or 600 of several
+// (90 fields of 2,400 tiles, some of them smooth, lose 3 to 7 %).
 constexpr unsigned kNoisyField = 48;
 constexpr uint32_t kAloneTiles = 2048;
+constexpr uint32_t kFewTiles = 600;
 
 // And calls of at most this many tiles leave the pair pass out, which is a
 // launch more (64^3: 110 -> 92 us, 100x90x80 Perlin 72 -> 69; at 500 tiles
@@ -1613,7 +1614,8 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
              const uint32_t *__restrict__ tfield, const Seg *__restrict__ seg,
              const uint32_t *__restrict__ R, unsigned long long *ctr,
              uint32_t *tstat, uint16_t *tlist, uint32_t *cidx,
-             const unsigned long long *alone, unsigned long long *dcells) {
+             const unsigned long long *fctr, int nsum,
+             unsigned long long *dcells) {
   static_assert(C::TZ % 4 == 0, "four planes per index word");
   __shared__ Decode<C> s;
   __shared__ uint32_t s_fresh[C::kThreads / 64];
@@ -1630,9 +1632,11 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
   const unsigned inside = min(C::TX, (int)g.X - t.x0) *
                           min(C::TY, (int)g.Y - t.y0) *
                           min(C::TZ, (int)g.Z - t.z0);
+  unsigned long long extrema = 0;  // of the whole call (nsum 0: not asked)
+  for (int i = 0; i < nsum; ++i)
+    extrema += fctr[i * kFieldCtrs + kFMaxima] + fctr[i * kFieldCtrs + kFMinima];
   if ((ts[0] + ts[1] > kPairExtrema && inside > kPairLimit) ||
-      (alone && alone[kFMaxima] + alone[kFMinima] >
-                    (unsigned long long)kNoisyField * g.ntiles)) {
+      extrema > (unsigned long long)kNoisyField * gridDim.x) {
     if (tid == 0) ts[2] = kTilePending;  // uniform over the block
     return;
   }
@@ -2420,7 +2424,8 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
       MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
                 (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
                     fds, tfield, seg, next, ctr, tstat, tlist, cidx,
-                    nfields == 1 && nt <= kAloneTiles ? fctr : nullptr,
+                    fctr,
+                    nt <= (nfields == 1 ? kAloneTiles : kFewTiles) ? nfields : 0,
                     dcells)));
     const unsigned sb =
         std::min<uint64_t>((uint64_t)nt * (C::TZ / kSlabZ), kSlabBlocks);
