@@ -31,10 +31,13 @@
 //                 every exit's successors to a final value -- the paper's
 //                 compression of the ghost graph after the exchange.
 //   tile_pairs    per tile: decode every vertex's final (asc, desc) pair from
-//                 its codes and the tile's resolved exits, dedupe in LDS, and
-//                 insert into the field's hash table keeping the smallest id;
-//   tile_write    the same decode, then asc, desc and the cell id per vertex
-//                 (the paper's relabelling pass, Alg. 2).
+//                 its codes and the tile's resolved exits, write the labels
+//                 (the paper's relabelling pass, Alg. 2), dedupe the pairs in
+//                 LDS, and insert them into the field's hash table keeping the
+//                 smallest id;
+//   tile_slabs    the same for tiles with more pairs than that table takes, in
+//                 slabs with a slot per vertex;
+//   tile_write    the cell id of every vertex, from its pair's number or slot.
 #include <climits>
 #include <cstdlib>
 #include <cstring>
@@ -1775,8 +1778,8 @@ k_tile_pairs(const FieldDev *__restrict__ fds,
 // the latency of those round trips on small fields and the rate of random
 // atomics on large ones.  With one thread inserting, and later looking up, its
 // 16 vertices in turn, a 64^3 field's 32 tiles took 86 us in the pair pass and
-// 64 us in the output pass, 64 fields of 32..256 1.11 and 0.57 ms; now pairs,
-// slabs and output take 34 + 22 + 9 us and 0.34 + 0.38 + 0.25 ms.
+// 64 us in the output pass, 64 fields of 32..256 1.11 and 0.57 ms; now slabs
+// and output take 23 + 9 us, and pairs, slabs and output 0.31 + 0.43 + 0.27 ms.
 //
 // The grid strides over the slabs; each wave reads the marks of 64 of its
 // block's slabs at once.  The second launch (`again`) does nothing unless the
@@ -2034,11 +2037,6 @@ k_tile_write(const FieldDev *__restrict__ fds,
     if (A) plane_ptr(A, g, t.z0 + lz)[col] = a;
     if (D) plane_ptr(D, g, t.z0 + lz)[col] = d;
   }
-}
-
-__global__ void k_fill_u32(uint32_t *p, uint32_t n, uint32_t value) {
-  uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) p[i] = value;
 }
 
 __global__ void k_fill_u64(unsigned long long *p, uint32_t n,
