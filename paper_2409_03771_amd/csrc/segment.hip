@@ -1518,9 +1518,14 @@ __device__ __forceinline__ int pair_slot(unsigned long long *skey,
                                          unsigned long long key,
                                          uint16_t *dense = nullptr) {
   // The slot is local to the tile, so a multiply-free hash of the two
-  // labels serves (the global table keeps its 64-bit mix).
+  // labels serves (the global table keeps its 64-bit mix).  Every bit of a
+  // label counts: with X = Y = 1024 the z of an extremum is its bits 20 and up,
+  // and without them pairs that differ in z alone ran out of probes, which
+  // sends the tile to the slab pass (1024^3 Perlin noise: 14.5 ms without the
+  // z bits, 13.6 ms with them).
   const uint32_t a = (uint32_t)(key >> 32), d = (uint32_t)key;
-  uint32_t h = (a ^ (a >> 10) ^ (d << 3) ^ (d >> 7)) & (kPairSlots - 1);
+  uint32_t h = (a ^ (a >> 10) ^ (a >> 20) ^ (d << 3) ^ (d >> 7) ^ (d >> 17)) &
+               (kPairSlots - 1);
 #pragma unroll 1
   for (int probe = 0; probe < kPairProbes; ++probe) {
     unsigned long long cur = skey[h];
