@@ -149,6 +149,15 @@ int enter_sync(msc_ctx *ctx, hipStream_t s) {
   return msc::begin_call(ctx, s);
 }
 
+// Exit of such a call: where it fails, the kernels that it has queued may still
+// run, and neither the next call (which may come on another stream and carve
+// the same workspace) nor the caller (who may free the outputs) waits for them,
+// so it does.
+int leave_sync(int rc, hipStream_t s) {
+  if (rc != MSC_OK) (void)hipStreamSynchronize(s);
+  return rc;
+}
+
 int check_dims(const int64_t dims[3], int64_t *n) {
   if (!dims) return MSC_EINVAL;
   for (int i = 0; i < 3; ++i)
@@ -320,9 +329,11 @@ int msc_segment_ranks(msc_ctx *ctx, const float *field, const int64_t dims[3],
   if (ranks < 1 || ranks > dims[2]) return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::segment_ranks_run(ctx, field, dims, ranks, asc, desc, ms,
-                                static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::segment_ranks_run(ctx, field, dims, ranks, asc, desc, ms, s),
+      s);
 }
 
 int msc_segment_csr(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
@@ -334,9 +345,11 @@ int msc_segment_csr(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
     return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::segment_csr_run(ctx, n, row_ptr, col_idx, field, asc, desc, ms,
-                              static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::segment_csr_run(ctx, n, row_ptr, col_idx, field, asc, desc, ms, s),
+      s);
 }
 
 int msc_segment_batched(msc_ctx *ctx, int nfields, const msc_field *fields,
@@ -633,9 +646,12 @@ int cc_label_grid_ranks(msc_ctx *ctx, const uint8_t *mask,
   if (ranks < 1 || ranks > dims[2]) return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::cc_grid_ranks_run(ctx, mask, dims[0], dims[1], dims[2], ranks,
-                                labels, static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::cc_grid_ranks_run(ctx, mask, dims[0], dims[1], dims[2], ranks,
+                             labels, s),
+      s);
 }
 
 int msc_critical_points(msc_ctx *ctx, const float *field,
@@ -646,9 +662,9 @@ int msc_critical_points(msc_ctx *ctx, const float *field,
   if (n > INT32_MAX) return MSC_ERANGE;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::critical_points_run(ctx, field, dims, code,
-                                  static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(msc::critical_points_run(ctx, field, dims, code, s), s);
 }
 
 int msc_extremum_graph(msc_ctx *ctx, const float *field, const int64_t dims[3],
@@ -661,9 +677,12 @@ int msc_extremum_graph(msc_ctx *ctx, const float *field, const int64_t dims[3],
   if (n > INT32_MAX) return MSC_ERANGE;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::extremum_graph_run(ctx, field, dims, asc, desc, edges, capacity,
-                                 count, static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::extremum_graph_run(ctx, field, dims, asc, desc, edges, capacity,
+                              count, s),
+      s);
 }
 
 int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
@@ -674,10 +693,12 @@ int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
   if (ntets > 0 && !tets) return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::csr_from_tets_run(ctx, n, ntets, tets, row_ptr, col_idx,
-                                capacity, nnz,
-                                static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::csr_from_tets_run(ctx, n, ntets, tets, row_ptr, col_idx, capacity,
+                             nnz, s),
+      s);
 }
 
 int cc_label_csr(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
@@ -689,9 +710,11 @@ int cc_label_csr(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   if (!row_ptr || !labels) return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::cc_csr_run(ctx, n, row_ptr, col_idx, mask, labels,
-                         static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(
+      msc::cc_csr_run(ctx, n, row_ptr, col_idx, mask, labels, s),
+      s);
 }
 
 int msc_pointer_jump(msc_ctx *ctx, int64_t *d, int64_t n, int rounds,
@@ -701,9 +724,9 @@ int msc_pointer_jump(msc_ctx *ctx, int64_t *d, int64_t n, int rounds,
   if (!d) return MSC_EINVAL;
   DeviceGuard g(ctx->device);
   if (!g.ok) return MSC_EHIP;
-  MSC_TRY(enter_sync(ctx, static_cast<hipStream_t>(stream)));
-  return msc::jump_run(ctx, d, n, rounds, synchronous,
-                       static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  MSC_TRY(enter_sync(ctx, s));
+  return leave_sync(msc::jump_run(ctx, d, n, rounds, synchronous, s), s);
 }
 
 }  // extern "C"

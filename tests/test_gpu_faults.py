@@ -118,3 +118,53 @@ def test_runtime_failure_in_the_queue(msc, after):
                 np.testing.assert_array_equal(got, O.cc_grid(a)[0])
             srv.release(t)
         assert srv.info()["arena_used"] == 0
+
+
+@pytest.mark.parametrize("kind,after", [
+    (1, 1),    # the pair table's allocation, with the compression queued
+    (2, 6),    # a runtime call after the kernels' launches
+])
+def test_csr_call_that_fails_leaves_nothing_running(msc, kind, after):
+    """A CSR segmentation that fails between its passes returns with its
+    stream drained, and a call on another stream, which carves the same
+    memory, is exact."""
+    n = 120
+    d = synth.kuhn_csr(n, seed=3, nbumps=9, permute=False)
+    rng = np.random.default_rng(2)
+    big = [torch.from_numpy(a).cuda() for a in
+           (d["row_ptr"], d["col_idx"],
+            rng.permutation(n ** 3).astype(np.float32))]
+    s = synth.kuhn_csr(24, seed=4, nbumps=6)
+    f = np.empty_like(s["field"])
+    f[s["perm"]] = s["field"]
+    small = [torch.from_numpy(a).cuda() for a in
+             (s["row_ptr"], s["col_idx"], f)]
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def call(ctx, g, stream):
+        outs = [torch.empty(g[2].numel(), dtype=torch.int32, device="cuda")
+                for _ in range(3)]
+        torch.cuda.synchronize()
+        rc = msc._lib.msc_segment_csr(
+            ctx, g[2].numel(), *(ctypes.c_void_p(t.data_ptr())
+                                 for t in (*g, *outs)),
+            ctypes.c_void_p(stream.cuda_stream))
+        return rc, outs
+
+    ctx = ctypes.c_void_p()
+    assert msc._lib.msc_create(ctypes.byref(ctx), 0) == msc.MSC_OK
+    try:
+        msc.debug_inject(kind, after)
+        rc, _ = call(ctx, big, one)
+        idle = one.query()
+        msc.debug_inject(kind, -1)
+        assert rc == (msc.MSC_ENOMEM if kind == 1 else msc.MSC_EHIP)
+        assert idle, "kernels of the failed call still run"
+        rc, outs = call(ctx, small, two)
+        assert rc == msc.MSC_OK
+        torch.cuda.synchronize()
+        for name, g, w in zip(("asc", "desc", "ms"), outs,
+                              O.segment_csr(s["row_ptr"], s["col_idx"], f)):
+            np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=name)
+    finally:
+        msc._lib.msc_destroy(ctx)
