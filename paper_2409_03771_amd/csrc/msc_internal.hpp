@@ -51,6 +51,7 @@ enum Counter : int {
   kCtrChanged = 0,   // set nonzero by a round that changed something
   kCtrGiant = 1,     // CSR components: the root most of a sample has (32 bits)
   kCtrCells = 2,     // vertices that are their own cell label
+  kCtrOpen = 3,      // CSR segmentation: a walk has not reached its root yet
   kCtrExits = 5,     // exits over all tiles (from the scan)
   kCtrBadIndex = 6,  // out-of-range CSR column seen
   kCtrOverflow = 7,  // pair table full (bit 0), broken exit chain (bit 1),

@@ -2697,6 +2697,7 @@ __global__ void __launch_bounds__(kBlock)
 k_csr_pairs(uint64_t n, int per, const int32_t *__restrict__ asc,
             const int32_t *__restrict__ desc, unsigned long long *keys,
             int32_t *vals, uint32_t mask, unsigned long long *ctr) {
+  if (ctr[kCtrOpen]) return;  // the labels are not final yet
   constexpr int K = kPairSlots / kBlock;
   __shared__ unsigned long long skey[kPairSlots];
   __shared__ int32_t sval[kPairSlots];
@@ -3137,10 +3138,14 @@ k_csr_steepest(int64_t n, const int64_t *__restrict__ rp,
 // ancestor and successors climb the (f, id) order strictly, so concurrent
 // chases agree and end, also on the older values that a cached load returns.
 // No final value is written: a halving store may land after another thread's,
-// so a root written here could be overwritten by an older ancestor.
+// so a root written here could be overwritten by an older ancestor.  A chase
+// gives up after kHalvings steps: the pass only shortens paths, and a path that
+// leads through vertices whose threads have not started has nothing to halve.
 __device__ __forceinline__ int32_t ld_near(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+constexpr int kHalvings = 256;
 
 __global__ void __launch_bounds__(kBlock)
 k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
@@ -3148,7 +3153,7 @@ k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
   if (v >= n) return;
   int32_t xa = (int32_t)v, xd = (int32_t)v;
   bool ea = false, ed = false;
-  while (!(ea && ed)) {
+  for (int k = 0; k < kHalvings && !(ea && ed); ++k) {
     // A chase that has ended reloads its last entries harmlessly.
     const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
     const int32_t ga = ld_near(&A[pa]), gd = ld_near(&D[pd]);
@@ -3173,27 +3178,59 @@ k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
 
 // Every vertex walks up both forests to its roots and writes its own two
 // entries: only the owner writes an entry, so a concurrent reader sees the old
-// pointer or the root, both ancestors, and a walk that meets a vertex that is
-// done ends there.  Up to kWalkOnly vertices that alone is enough: a walk meets
-// a finished vertex within ten steps once a tenth are done, and the halving
-// stores cost more than the steps they save (100^3: 0.92 ms a call instead of
-// 1.21; 208^3, where the gathers miss the caches: 1.83 ms against 1.71 for
-// both passes).
+// pointer or one further up, both ancestors, and a walk that meets a vertex that
+// is done ends there.  Up to kWalkOnly vertices of a mesh that alone is enough:
+// a walk meets a finished vertex within ten steps once a tenth are done, and the
+// halving stores cost more than the steps they save (100^3: 0.92 ms a call
+// instead of 1.21; 208^3, where the gathers miss the caches: 1.83 ms against
+// 1.71 for both passes).
+//
+// Paths may also be long (a monotone field along a curve: as long as the curve).
+// So a walk that has not ended after kLeg steps writes how far it has come into
+// its own entries and goes on with loads that see what the others have written,
+// up to kLegs times: along vertices whose threads run, each leg then steps over
+// all that the leg before covered.  Where it leads through vertices whose
+// threads have not started it may still not end; it is then left at an ancestor
+// and reported, and the host runs the pass again.  Every entry is then at least
+// kLeg * kLegs links further up per link it followed, so a few passes do for any
+// n.  A call on a monotone curve of 1M vertices, ids in no order, takes 0.6 ms
+// (2.4 s when walked link by link, 2.9 ms with halving alone, which at ids in
+// order takes 24 s: the paths lead into vertices that start last).
 constexpr int64_t kWalkOnly = 1 << 22;
+constexpr int kLeg = 32, kLegs = 16;
 
 __global__ void __launch_bounds__(kBlock)
-k_csr_roots(int64_t n, int32_t *A, int32_t *D) {
+k_csr_roots(int64_t n, int32_t *A, int32_t *D, unsigned long long *ctr) {
   const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  int32_t xa = (int32_t)v, xd = (int32_t)v;
-  for (;;) {
-    const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
-    if (pa == xa && pd == xd) break;
-    xa = pa;  // a walk that has ended reloads its root harmlessly
-    xd = pd;
+  bool open = v < n;
+  if (open) {
+    int32_t xa = (int32_t)v, xd = (int32_t)v;
+#pragma unroll 1
+    for (int k = 0; k < kLeg; ++k) {
+      const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
+      open = pa != xa || pd != xd;
+      if (!open) break;
+      xa = pa;  // a walk that has ended reloads its root harmlessly
+      xd = pd;
+    }
+#pragma unroll 1
+    for (int leg = 1; open && leg < kLegs; ++leg) {
+      __hip_atomic_store(&A[v], xa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&D[v], xd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+      for (int k = 0; k < kLeg; ++k) {
+        const int32_t pa = (int32_t)load_dev((const uint32_t *)&A[xa]),
+                      pd = (int32_t)load_dev((const uint32_t *)&D[xd]);
+        open = pa != xa || pd != xd;
+        if (!open) break;
+        xa = pa;
+        xd = pd;
+      }
+    }
+    __hip_atomic_store(&A[v], xa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&D[v], xd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __hip_atomic_store(&A[v], xa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&D[v], xd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__ballot(open) && (threadIdx.x & 63) == 0) atomicOr(ctr + kCtrOpen, 1ull);
 }
 
 }  // namespace
@@ -3236,8 +3273,22 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   if (n > kWalkOnly)
     MSC_PHASE(ctx, s, "csr_compress", 16.0 * n,
               (k_csr_compress<<<nblk, kBlock, 0, s>>>(n, A, D)));
-  MSC_PHASE(ctx, s, "csr_roots", 16.0 * n,
-            (k_csr_roots<<<nblk, kBlock, 0, s>>>(n, A, D)));
+  // The outcome of the walks is read back with the call's other counters, and
+  // only paths longer than a pass takes cost a wait of their own.
+  auto roots_pass = [&]() -> int {
+    MSC_PHASE(ctx, s, "csr_roots", 16.0 * n,
+              (k_csr_roots<<<nblk, kBlock, 0, s>>>(n, A, D, ctx->dctr)));
+    return MSC_OK;
+  };
+  auto finish_roots = [&]() -> int {
+    while (ctx->hctr[kCtrOpen]) {
+      k_fill_u64<<<1, kBlock, 0, s>>>(ctx->dctr + kCtrOpen, 1, 0ull);
+      MSC_TRY(roots_pass());
+      MSC_TRY(read_counters(ctx, s));
+    }
+    return MSC_OK;
+  };
+  MSC_TRY(roots_pass());
   MSC_HIP_TRY(hipEventSynchronize(ctx->done));
   const uint64_t nmax = ctx->hctr[kCtrRootsMax], nmin = ctx->hctr[kCtrRootsMin];
   const bool bad = ctx->hctr[kCtrBadIndex], nan = ctx->hctr[kCtrNaN];
@@ -3245,7 +3296,8 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   if (ms && !bad && !nan) {
     // Pair table: first capacity from the extremum counts, grown fourfold
     // while the pair pass overflows.  The cell pass is queued behind it
-    // without a look at the outcome; after an overflow both run again.
+    // without a look at the outcome; after an overflow, or where the walks had
+    // not ended (the pair pass then does nothing), both run again.
     uint64_t cap = table_first_capacity((uint64_t)n, nmax, nmin,
                                         ctx->table_first);
     const uint64_t full = table_capacity((uint64_t)n, nmax, nmin);
@@ -3270,17 +3322,21 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
                  k_rank_roots_sum<<<sum_grid(nblk), 1024, 0, s>>>(
                      roots, nblk, ctx->dctr + kCtrCells, nullptr)));
       MSC_TRY(read_counters(ctx, s));
-      if (!ctx->hctr[kCtrOverflow]) {
+      if (ctx->hctr[kCtrOpen]) {
+        MSC_TRY(finish_roots());
+      } else if (!ctx->hctr[kCtrOverflow]) {
         cells = (int64_t)ctx->hctr[kCtrCells];
         break;
+      } else {
+        if (cap >= full) return MSC_ENOMEM;
+        cap = cap * 4 < full ? cap * 4 : full;
       }
-      if (cap >= full) return MSC_ENOMEM;
-      cap = cap * 4 < full ? cap * 4 : full;
       k_fill_u64<<<1, kBlock, 0, s>>>(ctx->dctr + kCtrOverflow, 1, 0ull);
       k_fill_u64<<<1, kBlock, 0, s>>>(ctx->dctr + kCtrCells, 1, 0ull);
     }
   } else {
     MSC_TRY(read_counters(ctx, s));
+    if (!bad && !nan) MSC_TRY(finish_roots());
   }
   if (bad) return MSC_EINVAL;
   if (nan) return MSC_ENAN;

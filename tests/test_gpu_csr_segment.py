@@ -174,3 +174,77 @@ def test_sizes_against_the_grid(msc, X, Y, kind):
     wt = msc.last_stats()
     for k in ("n_maxima", "n_minima", "n_cells"):
         assert st[k] == wt[k], k
+
+
+def path_graph(n, order):
+    """A curve of n vertices: row_ptr, col_idx and, per position along it, the
+    vertex id."""
+    i = np.arange(n)
+    ids = (i if order == "in order" else i[::-1].copy() if order == "reversed"
+           else np.random.default_rng(n).permutation(n))
+    pos = np.empty(n, np.int64)
+    pos[ids] = i
+    nb = np.stack([np.where(pos > 0, ids[np.maximum(pos - 1, 0)], -1),
+                   np.where(pos < n - 1, ids[np.minimum(pos + 1, n - 1)], -1)],
+                  1)
+    nb.sort(axis=1)
+    rp = np.zeros(n + 1, np.int64)
+    rp[1:] = np.cumsum((nb >= 0).sum(1))
+    return rp, nb[nb >= 0].astype(np.int32), ids
+
+
+def along_path(ids, along):
+    """asc, desc and ms on a curve, by doubling (the oracle follows such paths
+    link by link for every vertex)."""
+    n = ids.size
+    out = []
+    for sign in (1, -1):
+        to = np.arange(n)
+        for d in (-1, 1):
+            u = np.arange(n) + d
+            ok = (u >= 0) & (u < n)
+            u = np.clip(u, 0, n - 1)
+            fu, ft = sign * along[u], sign * along[to]
+            up = (fu > ft) | ((fu == ft) & (sign * ids[u] > sign * ids[to]))
+            to = np.where(ok & up, u, to)
+        while not np.array_equal(to[to], to):
+            to = to[to]
+        root = np.empty(n, np.int64)
+        root[ids] = ids[to]
+        out.append(root)
+    _, first, inv = np.unique(out[0] * n + out[1], return_index=True,
+                              return_inverse=True)
+    return out[0], out[1], first[inv]
+
+
+@pytest.mark.parametrize("want", [("asc", "desc", "ms"), ("asc", "desc")])
+@pytest.mark.parametrize("n", [511, 70_000, 1 << 20, (1 << 22) + 77])
+@pytest.mark.parametrize("order", ["in order", "reversed", "random"])
+def test_long_paths(msc, n, order, want):
+    """A field that climbs along a curve, whose paths are as long as the curve,
+    and one that climbs and falls in a few long stretches.  The time is bounded
+    well above what a call takes and well below what it takes to follow such
+    paths link by link (seconds at a million vertices)."""
+    rp, ci, ids = path_graph(n, order)
+    i = np.arange(n)
+    period = n // 3 + 7
+    for tag, along in (("ramp", i), ("waves", np.abs(i % period - period // 3))):
+        f = np.empty(n, np.float32)
+        f[ids] = along
+        g = [torch.from_numpy(a).cuda() for a in (rp, ci, f)]
+        msc.segment_csr(*g, want=want)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        got = msc.segment_csr(*g, want=want)
+        b.record()
+        b.synchronize()
+        assert a.elapsed_time(b) < 400.0, tag
+        ref = along_path(ids, along)
+        for name, x, w in zip(("asc", "desc", "ms"), got, ref):
+            if name in want:
+                np.testing.assert_array_equal(x.cpu().numpy(), w,
+                                              err_msg=f"{tag} {name}")
+            else:
+                assert x is None
+        if "ms" in want:
+            assert msc.last_stats()["n_cells"] == len(np.unique(ref[2]))
