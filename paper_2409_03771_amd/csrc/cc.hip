@@ -764,11 +764,28 @@ k_csr_init(CsrGraph g, int32_t *__restrict__ P) {
   P[i] = best;
 }
 
+// Root of x if it is at most kLeg steps away, else -1 (the walk may grow as fast
+// as it goes on: other threads hook the roots that it reaches).
+constexpr int kLeg = 32;
+
+__device__ __forceinline__ int32_t uf_root_near(const int32_t *P, int32_t x) {
+#pragma unroll 1
+  for (int k = 0; k < kLeg; ++k) {
+    const int32_t p = __hip_atomic_load(&P[x], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (p == x) return x;
+    x = p;
+  }
+  return -1;
+}
+
 // One attempt to join v's tree with that of one entry of its row, for one in
 // `stride` waves of vertices: the larger root is hooked if it still is a root.
-// Another thread may have hooked it first; later rounds and the pass over all
-// edges make good what is left then, where retrying until the trees are one has
-// a million threads queue up on a handful of roots (1.5 ms).
+// Another thread may have hooked it first, or the roots may have moved far; later
+// rounds and the pass over all edges make good what is left then, where retrying
+// until the trees are one has a million threads queue up on a handful of roots
+// (1.5 ms), and walking on along a curve with rising ids, where the hooks form
+// one chain, takes up to 20 ms for 1M vertices.
 __global__ void __launch_bounds__(kBlock)
 k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
   const int64_t w = gid() >> 6;
@@ -782,9 +799,9 @@ k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
   if (u < 0 || (int64_t)u >= g.n) return;
   int32_t b = P[u];
   if (b < 0 || a == b) return;
-  a = uf_root<int32_t>(P, a);
-  b = uf_root<int32_t>(P, b);
-  if (a == b) return;
+  a = uf_root_near(P, a);
+  b = uf_root_near(P, b);
+  if (a == b || a < 0 || b < 0) return;
   const int32_t lo = a < b ? a : b;
   int32_t hi = a < b ? b : a;
   if (ld_dev(&P[hi]) == hi)
@@ -793,16 +810,38 @@ k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
                                          __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Every vertex straight to its root.
+// Every vertex straight to its root.  Most trees are shallow, but hooks and
+// joins can also leave a chain through half the vertices (ids that rise along a
+// curve).  So a walk that has not ended after kLeg steps writes how far it has
+// come into its own entry, which nobody else writes, and goes on with loads that
+// see what the others have written: a leg then steps over all that the leg
+// before covered (the vertices below, whose threads started earlier, do the
+// same).
 __global__ void __launch_bounds__(kBlock)
 k_csr_compress(int64_t n, int32_t *P) {
   const int64_t v = gid();
   if (v >= n) return;
-  if (__hip_atomic_load(&P[v], __ATOMIC_RELAXED,
-                        __HIP_MEMORY_SCOPE_WORKGROUP) < 0)
-    return;
-  __hip_atomic_store(&P[v], uf_root<int32_t>(P, (int32_t)v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
+  int32_t x = __hip_atomic_load(&P[v], __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_WORKGROUP);
+  if (x < 0) return;
+  bool open = true;
+#pragma unroll 1
+  for (int k = 0; open && k < kLeg; ++k) {
+    const int32_t p = __hip_atomic_load(&P[x], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+    open = p != x;
+    x = p;
+  }
+  while (open) {
+    __hip_atomic_store(&P[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+    for (int k = 0; open && k < kLeg; ++k) {
+      const int32_t p = ld_dev(&P[x]);
+      open = p != x;
+      x = p;
+    }
+  }
+  __hip_atomic_store(&P[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The root that a sample of the vertices names most often (-2: none is in the
