@@ -3132,58 +3132,18 @@ k_csr_steepest(int64_t n, const int64_t *__restrict__ rp,
   }
 }
 
-// Path halving along both of a vertex's chases, side by side (the cost is the
-// gathers' latency and rate; one after the other, at system scope, 208^3
-// vertices took 1.77 ms, this way 1.56).  An entry only ever moves to an
-// ancestor and successors climb the (f, id) order strictly, so concurrent
-// chases agree and end, also on the older values that a cached load returns.
-// No final value is written: a halving store may land after another thread's,
-// so a root written here could be overwritten by an older ancestor.  A chase
-// gives up after kHalvings steps: the pass only shortens paths, and a path that
-// leads through vertices whose threads have not started has nothing to halve.
 __device__ __forceinline__ int32_t ld_near(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-constexpr int kHalvings = 256;
-
-__global__ void __launch_bounds__(kBlock)
-k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  int32_t xa = (int32_t)v, xd = (int32_t)v;
-  bool ea = false, ed = false;
-  for (int k = 0; k < kHalvings && !(ea && ed); ++k) {
-    // A chase that has ended reloads its last entries harmlessly.
-    const int32_t pa = ld_near(&A[xa]), pd = ld_near(&D[xd]);
-    const int32_t ga = ld_near(&A[pa]), gd = ld_near(&D[pd]);
-    if (!ea) {
-      ea = ga == pa;
-      if (!ea) {
-        __hip_atomic_store(&A[xa], ga, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        xa = ga;
-      }
-    }
-    if (!ed) {
-      ed = gd == pd;
-      if (!ed) {
-        __hip_atomic_store(&D[xd], gd, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        xd = gd;
-      }
-    }
-  }
 }
 
 // Every vertex walks up both forests to its roots and writes its own two
 // entries: only the owner writes an entry, so a concurrent reader sees the old
 // pointer or one further up, both ancestors, and a walk that meets a vertex that
-// is done ends there.  Up to kWalkOnly vertices of a mesh that alone is enough:
-// a walk meets a finished vertex within ten steps once a tenth are done, and the
-// halving stores cost more than the steps they save (100^3: 0.92 ms a call
-// instead of 1.21; 208^3, where the gathers miss the caches: 1.83 ms against
-// 1.71 for both passes).
+// is done ends there: on a mesh within ten steps once a tenth are done.  The cost
+// is the gathers' latency and rate, so both walks go side by side on cached
+// loads (an older value is still an ancestor); halving the paths first costs more
+// in stores than it saves in steps (165^3 vertices: 2.00 ms a call with halving,
+// 1.78 without, 208^3 3.90 and 3.82, 250^3 6.94 and 6.88).
 //
 // Paths may also be long (a monotone field along a curve: as long as the curve).
 // So a walk that has not ended after kLeg steps writes how far it has come into
@@ -3196,7 +3156,6 @@ k_csr_compress(int64_t n, int32_t *A, int32_t *D) {
 // n.  A call on a monotone curve of 1M vertices, ids in no order, takes 0.6 ms
 // (2.4 s when walked link by link, 2.9 ms with halving alone, which at ids in
 // order takes 24 s: the paths lead into vertices that start last).
-constexpr int64_t kWalkOnly = 1 << 22;
 constexpr int kLeg = 32, kLegs = 16;
 
 __global__ void __launch_bounds__(kBlock)
@@ -3270,9 +3229,6 @@ int segment_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   MSC_HIP_TRY(hipMemcpyAsync(ctx->hctr, ctx->dctr, kNumCounters * 8,
                              hipMemcpyDeviceToHost, s));
   MSC_HIP_TRY(hipEventRecord(ctx->done, s));
-  if (n > kWalkOnly)
-    MSC_PHASE(ctx, s, "csr_compress", 16.0 * n,
-              (k_csr_compress<<<nblk, kBlock, 0, s>>>(n, A, D)));
   // The outcome of the walks is read back with the call's other counters, and
   // only paths longer than a pass takes cost a wait of their own.
   auto roots_pass = [&]() -> int {
