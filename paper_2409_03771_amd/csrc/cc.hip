@@ -2014,11 +2014,33 @@ struct Walk {
   int zc;                      // planes per walk
 };
 
-// idx * 2 + (the lane's bit of m).
-__device__ __forceinline__ uint32_t push_bit(uint32_t idx,
-                                             unsigned long long m) {
-  asm("v_addc_co_u32 %0, vcc, %0, %0, %1" : "+v"(idx) : "s"(m) : "vcc");
-  return idx;
+// The lane's bits of 14 compares' masks as a number, m[0]'s highest.  The
+// compiler does not see what is inside an asm block, so the wait states that a
+// vector operation needs before it reads a mask that a compare has just written
+// stand at its start (two; inside, each mask is older than that).
+__device__ __forceinline__ uint32_t lane_bits(const unsigned long long (&m)[14]) {
+  uint32_t r = 0;
+  asm("s_nop 1\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %1\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %2\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %3\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %4\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %5\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %6\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %7\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %8\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %9\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %10\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %11\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %12\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %13\n"
+      "\tv_addc_co_u32 %0, vcc, %0, %0, %14"
+      : "+v"(r)
+      : "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3]), "s"(m[4]), "s"(m[5]),
+        "s"(m[6]), "s"(m[7]), "s"(m[8]), "s"(m[9]), "s"(m[10]), "s"(m[11]),
+        "s"(m[12]), "s"(m[13])
+      : "vcc");
+  return r;
 }
 
 __device__ __forceinline__ unsigned long long lanes(bool b) {
@@ -2084,21 +2106,15 @@ __device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
     nan |= v != v;
     // Neighbours in decreasing id; the ones with smaller ids than v are below
     // it when equal.
-    uint32_t s = 0;
-    s = push_bit(s, lanes(uph.xyh < v));
-    s = push_bit(s, lanes(uph.yh < v));
-    s = push_bit(s, lanes(uph.xh < v));
-    s = push_bit(s, lanes(up.c < v));
-    s = push_bit(s, lanes(curh.xyh < v));
-    s = push_bit(s, lanes(curh.yh < v));
-    s = push_bit(s, lanes(curh.xh < v));
-    s = push_bit(s, lanes(cur.xl <= v));
-    s = push_bit(s, lanes(cur.yl <= v));
-    s = push_bit(s, lanes(cur.xyl <= v));
-    s = push_bit(s, lanes(below.c <= v));
-    s = push_bit(s, lanes(below.xl <= v));
-    s = push_bit(s, lanes(below.yl <= v));
-    s = push_bit(s, lanes(below.xyl <= v));
+    const unsigned long long m[14] = {
+        lanes(uph.xyh < v), lanes(uph.yh < v),
+        lanes(uph.xh < v), lanes(up.c < v),
+        lanes(curh.xyh < v), lanes(curh.yh < v),
+        lanes(curh.xh < v), lanes(cur.xl <= v),
+        lanes(cur.yl <= v), lanes(cur.xyl <= v),
+        lanes(below.c <= v), lanes(below.xl <= v),
+        lanes(below.yl <= v), lanes(below.xyl <= v)};
+    const uint32_t s = lane_bits(m);
     const uint32_t planes = (z > 0 ? 0xfu : 0u) | 0x3f0u |
                             (z + 1 < w.Z ? 0x3c00u : 0u);  // uniform
     const uint32_t present = here & planes;
