@@ -1884,7 +1884,7 @@ constexpr uint32_t link_adj(int i) {
 // whose components are the remaining ones, so repeated lookups enumerate them.
 constexpr int kLinkSets = 1 << 14;
 
-struct LinkTables {
+struct alignas(16) LinkTables {  // read 16 bytes at a time (stage_ncomp)
   uint8_t ncomp[kLinkSets];
   uint16_t first[kLinkSets];
 };
@@ -2130,6 +2130,9 @@ __device__ __forceinline__ bool walk_links(const Walk &w, Use use) {
 
 // The count table in LDS, where both lookups of a vertex cost one read.
 __device__ __forceinline__ void stage_ncomp(uint8_t *t) {
+  static_assert(alignof(LinkTables) >= alignof(uint4) &&
+                    offsetof(LinkTables, ncomp) == 0 && kLinkSets % 16 == 0,
+                "whole aligned uint4s");
   const uint4 *src = reinterpret_cast<const uint4 *>(kLink.ncomp);
   for (int i = threadIdx.x; i < kLinkSets / 16; i += kWalkThreads)
     reinterpret_cast<uint4 *>(t)[i] = src[i];

@@ -77,3 +77,13 @@ def test_masks_are_read_two_wait_states_after_the_compare(code):
     assert sum(bool(re.match(r"\s*v_cmp_", s)) for s in lines) > 50, name
     bad = mask_hazards(lines)
     assert not bad, f"{name}: {len(bad)}, e.g. {bad[:3]}"
+
+
+def test_link_tables_are_aligned_for_their_wide_loads(code):
+    name, lines = code
+    if name != "cc.hip":
+        pytest.skip("the tables are in cc.hip")
+    at = next(i for i, s in enumerate(lines)
+              if re.match(r"_ZN\S*kLink\S*:", s))
+    align = next(s for s in reversed(lines[:at]) if ".p2align" in s)
+    assert int(re.search(r"\.p2align\s+(\d+)", align).group(1)) >= 4, align
