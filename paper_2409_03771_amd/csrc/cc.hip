@@ -1384,8 +1384,10 @@ int cc_grid_ranks_run(msc_ctx *ctx, const uint8_t *mask, int64_t X,
                       int64_t Y, int64_t Z, int ranks, int64_t *labels,
                       hipStream_t s) {
   const int64_t XY = X * Y, N = XY * Z;
-  const int64_t thickest = (Z + ranks - 1) / ranks;
-  MSC_TRY(reserve(ctx, ctx->ws, align256(XY * thickest * sizeof(uint16_t)) + 4096));
+  // Room for the thickest slab's tiles: no slab grows the workspace while the
+  // kernels of the ones before it are queued on it.
+  const msc_mask thickest{mask, {X, Y, (Z + ranks - 1) / ranks}, labels};
+  MSC_TRY(reserve(ctx, ctx->ws, cc_grid_workspace(1, &thickest)));
   for (int r = 0; r < ranks; ++r) {
     const int64_t z0 = r * Z / ranks, z1 = (r + 1) * Z / ranks;
     // No host round trip per slab: the slabs queue on the stream (the

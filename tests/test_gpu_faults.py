@@ -168,3 +168,28 @@ def test_csr_call_that_fails_leaves_nothing_running(msc, kind, after):
             np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=name)
     finally:
         msc._lib.msc_destroy(ctx)
+
+
+@pytest.mark.parametrize("X,Y,Z,ranks", [(513, 513, 33, 2), (513, 513, 50, 3)])
+def test_slabs_of_a_rank_call_share_one_workspace(msc, X, Y, Z, ranks):
+    """Slabs that cover different numbers of tile layers: the workspace is
+    taken once for the thickest, never grown with an earlier slab's kernels
+    queued on it (a second allocation would fail here)."""
+    mask = synth.random_field((X, Y, Z), seed=X + Z) > 0.4
+    t = torch.from_numpy(mask.astype(np.uint8)).cuda()
+    want = msc.cc_label_grid(t)
+    got = torch.empty(t.numel(), dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    dims = (ctypes.c_int64 * 3)(X, Y, Z)
+    ctx = ctypes.c_void_p()
+    assert msc._lib.msc_create(ctypes.byref(ctx), 0) == msc.MSC_OK
+    try:
+        msc.debug_inject(msc.INJECT_ENOMEM, 1)
+        rc = msc._lib.cc_label_grid_ranks(
+            ctx, ctypes.c_void_p(t.data_ptr()), dims, ranks,
+            ctypes.c_void_p(got.data_ptr()), None)
+        msc.debug_inject(msc.INJECT_ENOMEM, -1)
+        assert rc == msc.MSC_OK
+        assert torch.equal(got, want)
+    finally:
+        msc._lib.msc_destroy(ctx)
