@@ -477,6 +477,20 @@ MSC_API int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
                               int64_t *nnz, void *stream);
 
 /*
+ * The same with the columns' memory taken in the middle of the call, when their
+ * number is known: `alloc` is called once, on the calling thread, with `user`
+ * and the entry count (more than 0; a complex without edges needs none), and
+ * returns device memory for that many int32 (NULL: the call returns
+ * MSC_ENOMEM).  It must neither throw nor use `ctx`.  Otherwise as
+ * msc_csr_from_tets; MSC_EINVAL also for a NULL alloc.
+ */
+typedef void *(*msc_alloc_fn)(void *user, int64_t entries);
+MSC_API int msc_csr_from_tets_alloc(msc_ctx *ctx, int64_t n, int64_t ntets,
+                                    const int32_t *tets, int64_t *row_ptr,
+                                    msc_alloc_fn alloc, void *user,
+                                    int64_t *nnz, void *stream);
+
+/*
  * Connected components of an explicit graph in CSR form (the paper's
  * "explicit" CC on extracted geometry).
  *

@@ -685,9 +685,10 @@ int msc_extremum_graph(msc_ctx *ctx, const float *field, const int64_t dims[3],
       s);
 }
 
-int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
-                      const int32_t *tets, int64_t *row_ptr, int32_t *col_idx,
-                      int64_t capacity, int64_t *nnz, void *stream) {
+static int csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
+                         const int32_t *tets, int64_t *row_ptr,
+                         int32_t *col_idx, int64_t capacity, msc_alloc_fn alloc,
+                         void *user, int64_t *nnz, void *stream) {
   if (!ctx || n < 0 || ntets < 0 || !row_ptr || !nnz) return MSC_EINVAL;
   if (n > INT32_MAX || ntets > (INT64_MAX >> 6)) return MSC_ERANGE;
   if (ntets > 0 && !tets) return MSC_EINVAL;
@@ -697,8 +698,24 @@ int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
   MSC_TRY(enter_sync(ctx, s));
   return leave_sync(
       msc::csr_from_tets_run(ctx, n, ntets, tets, row_ptr, col_idx, capacity,
-                             nnz, s),
+                             alloc, user, nnz, s),
       s);
+}
+
+int msc_csr_from_tets(msc_ctx *ctx, int64_t n, int64_t ntets,
+                      const int32_t *tets, int64_t *row_ptr, int32_t *col_idx,
+                      int64_t capacity, int64_t *nnz, void *stream) {
+  return csr_from_tets(ctx, n, ntets, tets, row_ptr, col_idx, capacity, nullptr,
+                       nullptr, nnz, stream);
+}
+
+int msc_csr_from_tets_alloc(msc_ctx *ctx, int64_t n, int64_t ntets,
+                            const int32_t *tets, int64_t *row_ptr,
+                            msc_alloc_fn alloc, void *user, int64_t *nnz,
+                            void *stream) {
+  if (!alloc) return MSC_EINVAL;
+  return csr_from_tets(ctx, n, ntets, tets, row_ptr, nullptr, 0, alloc, user,
+                       nnz, stream);
 }
 
 int cc_label_csr(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,

@@ -1781,7 +1781,8 @@ int scan64(msc_ctx *ctx, const uint32_t *cnt, int64_t n, int64_t *out,
 
 int csr_from_tets_run(msc_ctx *ctx, int64_t n, int64_t ntets,
                       const int32_t *tets, int64_t *row_ptr, int32_t *col_idx,
-                      int64_t capacity, int64_t *nnz, hipStream_t s) {
+                      int64_t capacity, msc_alloc_fn alloc, void *user,
+                      int64_t *nnz, hipStream_t s) {
   const int64_t nb = (n + kScan - 1) / kScan;
   const int64_t ncand = 12 * ntets;
   MSC_TRY(reserve(ctx, ctx->ws, align256(n * 4) + align256((n + 1) * 8) +
@@ -1807,13 +1808,18 @@ int csr_from_tets_run(msc_ctx *ctx, int64_t n, int64_t ntets,
   if (n > 0)
     MSC_PHASE(ctx, s, "rows_distinct", 4.0 * ncand + 12.0 * n,
               (k_row_distinct<<<grid64(n, kRows), kRows, 0, s>>>(
-                  n, off, cand, cnt, col_idx != nullptr)));
+                  n, off, cand, cnt, col_idx || alloc)));
   MSC_PHASE(ctx, s, "rows_scan", 12.0 * n,
             (scan64(ctx, cnt, n, row_ptr, bsum, s)));
   MSC_TRY(read_counters(ctx, s, row_ptr + n));
   if (ctx->hctr[kCtrBadIndex]) return MSC_EINVAL;
   const int64_t total = (int64_t)ctx->hctr[kCtrExtra];
   *nnz = total;
+  if (alloc && total > 0) {
+    col_idx = static_cast<int32_t *>(alloc(user, total));
+    if (!col_idx) return MSC_ENOMEM;
+    capacity = total;
+  }
   if (col_idx && capacity >= total && total > 0) {
     MSC_PHASE(ctx, s, "rows_fill", 4.0 * ncand + 4.0 * total,
               (k_row_fill<<<grid64(n, kRows), kRows, 0, s>>>(

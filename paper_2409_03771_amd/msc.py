@@ -32,6 +32,7 @@ MSC_EBUDGET, MSC_EHIP, MSC_ECANCELED, MSC_EBUSY = 5, 6, 7, 8
 _P = ctypes.c_void_p
 _I64 = ctypes.c_int64
 _I32 = ctypes.c_int
+_ALLOC = ctypes.CFUNCTYPE(_P, _P, _I64)
 
 
 class msc_stats(ctypes.Structure):
@@ -86,6 +87,8 @@ _SIGS = {
                             ctypes.POINTER(_I64), _P], _I32),
     "msc_csr_from_tets": ([_P, _I64, _I64, _P, _P, _P, _I64,
                            ctypes.POINTER(_I64), _P], _I32),
+    "msc_csr_from_tets_alloc": ([_P, _I64, _I64, _P, _P, _ALLOC, _P,
+                                 ctypes.POINTER(_I64), _P], _I32),
     "cc_label_grid_ranks": ([_P, _P, ctypes.POINTER(_I64), _I32, _P, _P],
                             _I32),
     "cc_label_csr": ([_P, _I64, _P, _P, _P, _P, _P], _I32),
@@ -293,27 +296,32 @@ def extremum_graph(field: torch.Tensor, asc: torch.Tensor, desc: torch.Tensor,
 
 def csr_from_tets(n: int, tets: torch.Tensor, stream=None):
     """(row_ptr int64 [n+1], col_idx int32) of the 1-skeleton of the
-    tetrahedra `tets` (int32 [T, 4] on the device).
-
-    The entries go straight into a buffer of 16 per vertex (a tetrahedral
-    mesh has about 14 to 15.5), or 12 per tetrahedron where that is fewer and
-    always enough; a complex with more entries takes a second call with the
-    count of the first.  On 24.1M Kuhn tetrahedra one call takes 3.6 ms where
-    a counting call and a filling one took 6.6."""
+    tetrahedra `tets` (int32 [T, 4] on the device): one call, which takes the
+    columns' memory when it knows their number."""
     dev = tets.device
     row_ptr = torch.empty(n + 1, dtype=torch.int64, device=dev)
-    room = min(12 * (tets.numel() // 4), 16 * max(n, 0) + 4096)
-    try:
-        col = torch.empty(max(room, 1), dtype=torch.int32, device=dev)
-    except torch.OutOfMemoryError:  # the exact count may still fit
-        col = None
-    nnz = csr_from_tets_into(n, tets, row_ptr, col, stream)
-    if col is None or nnz > col.numel():
-        col = torch.empty(max(nnz, 1), dtype=torch.int32, device=dev)
-        csr_from_tets_into(n, tets, row_ptr, col, stream)
-    # The result does not hold on to a buffer far larger than itself.
-    return row_ptr, (col[:nnz] if 2 * nnz >= col.numel() else
-                     col[:nnz].clone())
+    col, failed = [], []
+
+    def alloc(_, entries):
+        try:
+            col.append(torch.empty(entries, dtype=torch.int32, device=dev))
+            return col[0].data_ptr()
+        except BaseException as e:  # must not leave through the C call
+            failed.append(e)
+            return None
+
+    nnz = _I64(0)
+    code = _lib.msc_csr_from_tets_alloc(
+        context(dev.index), int(n), int(tets.numel() // 4),
+        _dev_ptr(tets, torch.int32, "tets"),
+        _dev_ptr(row_ptr, torch.int64, "row_ptr"), _ALLOC(alloc), None,
+        ctypes.byref(nnz), _stream(tets, stream))
+    if failed:
+        raise failed[0]
+    _check(code, "msc_csr_from_tets")
+    if not col:
+        col.append(torch.empty(0, dtype=torch.int32, device=dev))
+    return row_ptr, col[0]
 
 
 def csr_from_tets_into(n, tets, row_ptr, col_idx, stream=None) -> int:

@@ -112,3 +112,45 @@ def test_block_edges(msc, n, ntets):
     if n >= 4 * ntets:
         tets = rng.permutation(n)[:4 * ntets].reshape(-1, 4).astype(np.int32)
     check(msc, n, tets, f"edges n={n} T={ntets}")
+
+
+@pytest.mark.parametrize("n,ntets", [(20 ** 3, None), (2000, 9000),
+                                     (130, 6000), (40, 1), (7, 0)])
+def test_result_owns_its_entries_alone(msc, monkeypatch, n, ntets):
+    """The columns lie in memory of exactly their size, for complexes with few
+    and with many entries per vertex, and no larger buffer is taken on the way
+    (the device needs room for the result alone)."""
+    if ntets is None:
+        tets = synth.kuhn_tets(20)
+    else:
+        tets = np.random.default_rng(ntets).integers(
+            0, n, size=(ntets, 4)).astype(np.int32)
+    t = torch.from_numpy(np.ascontiguousarray(tets, np.int32).reshape(-1, 4))
+    t = t.cuda()
+    wrp, wci = O.csr_from_tets(n, tets)
+    real, taken, full = torch.empty, [], [False]
+
+    def empty(*args, **kw):
+        if kw.get("dtype") == torch.int32:
+            if full[0]:
+                raise torch.OutOfMemoryError("as if the device were full")
+            taken.append(args[0])
+        return real(*args, **kw)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    rp, ci = msc.csr_from_tets(n, t, stream=side)
+    assert side.query()
+    assert taken == [wci.size]
+    assert ci.is_contiguous() and ci.dtype == torch.int32
+    assert ci.untyped_storage().nbytes() == 4 * ci.numel()
+    np.testing.assert_array_equal(rp.cpu().numpy(), wrp)
+    np.testing.assert_array_equal(ci.cpu().numpy(), wci)
+    if wci.size:
+        full[0] = True
+        with pytest.raises(torch.OutOfMemoryError):
+            msc.csr_from_tets(n, t)
+        full[0] = False
+    rp, ci = msc.csr_from_tets(n, t)
+    np.testing.assert_array_equal(ci.cpu().numpy(), wci)
