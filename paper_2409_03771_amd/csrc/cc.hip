@@ -2161,6 +2161,20 @@ k_critical(Walk w, uint8_t *__restrict__ code, unsigned long long *ctr) {
   flag_any(nan, ctr + kCtrNaN);
 }
 
+// The same with a vertex per thread, for grids that the walk does not suit.
+__global__ void __launch_bounds__(kBlock)
+k_critical_small(const float *__restrict__ f, int64_t X, int64_t Y, int64_t Z,
+                 uint8_t *__restrict__ code, unsigned long long *ctr) {
+  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  bool nan = false;
+  if (v < X * Y * Z) {
+    const LinkSets ls = link_sets(f, X, Y, Z, v);
+    code[v] = (uint8_t)(kLink.ncomp[ls.lower] | kLink.ncomp[ls.upper] << 4);
+    nan = ls.nan;
+  }
+  flag_any(nan, ctr + kCtrNaN);
+}
+
 // Edges of a vertex: one per component of a side that has two or more.
 __device__ __forceinline__ uint32_t edge_count(uint32_t lc, uint32_t uc) {
   return (uc >= 2 ? uc : 0u) + (lc >= 2 ? lc : 0u);
@@ -2376,6 +2390,17 @@ Walk make_walk(const float *f, const int64_t *dims, unsigned *blocks) {
   return w;
 }
 
+// The walk is for planes that fill a good part of its blocks (kWalkThreads
+// positions each) and for more than one of them: a block of a narrow plane
+// works, and stages its table, for few vertices, and a single plane is walked
+// with two neighbour planes that are not there.  Critical points of 4.2M
+// vertices, a vertex per thread / walked: planes of 8x8 positions 45 / 68 us,
+// 12x10 44 / 50, 140x1 44 / 48, 18x9 45 / 46, 16x12 45 / 44, 16x16 44 / 39, 64x64
+// 45 / 35; 1M vertices in a row 32 / 685; 4096x4096x1 99 / 110, 2048x2048x2
+// 63 / 54.  (A walk of the narrowest planes would also be of more threads than a
+// launch takes, 2^32, from Z = 2^27 on.)
+bool walk_suits(const Walk &w) { return w.XY >= 192 && w.Z > 1; }
+
 }  // namespace
 
 int critical_points_run(msc_ctx *ctx, const float *field, const int64_t *dims,
@@ -2385,7 +2410,10 @@ int critical_points_run(msc_ctx *ctx, const float *field, const int64_t *dims,
   const Walk w = make_walk(field, dims, &nb);
   MSC_TRY(clear_counters(ctx, s));
   MSC_PHASE(ctx, s, "critical", 5.0 * N,
-            (w.zc == 16
+            (!walk_suits(w)
+                 ? k_critical_small<<<grid_for(N), kBlock, 0, s>>>(
+                       field, dims[0], dims[1], dims[2], code, ctx->dctr)
+             : w.zc == 16
                  ? k_critical<16><<<nb, kWalkThreads, 0, s>>>(w, code, ctx->dctr)
                  : k_critical<4><<<nb, kWalkThreads, 0, s>>>(w, code,
                                                              ctx->dctr)));

@@ -115,3 +115,29 @@ def test_runs_and_walks(msc, dims, kind):
     finally:
         msc.set_workspace(None)
     np.testing.assert_array_equal(again, E, err_msg=f"{dims} small workspace")
+
+
+@pytest.mark.parametrize("dims", [(191, 1, 6), (192, 1, 6), (193, 1, 6),
+                                  (12, 16, 33), (16, 12, 1), (300, 200, 2),
+                                  (15, 1, 70), (1, 3, 200)])
+@pytest.mark.parametrize("levels", [None, 3])
+def test_walks_and_single_vertices(msc, dims, levels):
+    """On both sides of where planes are walked: their width and number."""
+    f = synth.random_field(dims, seed=sum(dims), levels=levels)
+    check(msc, f, f"{dims} levels={levels}")
+
+
+def test_longest_chain(msc):
+    """A chain of vertices along z, longer than a launch has blocks for where a
+    block takes 16 planes."""
+    n = (1 << 27) + 37
+    print(f"[critical] 1x1x{n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    f = torch.randint(0, 50, (n,), generator=g, device="cuda").float()
+    code = msc.critical_points(f.reshape(n, 1, 1))
+    low = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    low[1:] += f[:-1] <= f[1:]   # the neighbour of smaller id: below when equal
+    low[:-1] += f[1:] < f[:-1]
+    here = torch.full((n,), 2, dtype=torch.uint8, device="cuda")
+    here[0] = here[-1] = 1
+    assert torch.equal(code, low | (here - low) << 4)
