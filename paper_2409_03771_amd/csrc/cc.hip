@@ -2266,24 +2266,36 @@ k_egraph_mark(Walk w, unsigned long long *__restrict__ marks,
   flag_any(nan, ctr + kCtrNaN);
 }
 
-// A wave takes K consecutive runs (at most 64), lists their marked vertices in
+// A wave takes K consecutive runs (at most 31), lists their marked vertices in
 // LDS, and works through the list 64 at a time, so that its lanes are full
 // however the marks lie.  The edges of its runs are one contiguous stretch of
-// the output, in the list's order.  K is what holds about 32 edges: with more
-// the long lists of noisy regions are left to few waves, with fewer the lanes
-// are idle.  At 512^3 Perlin noise (0.9 % of the vertices marked) K = 64 takes
-// 0.12 ms and K = 8 0.44, at 512^3 Gaussian sums (5 %, in clusters) 0.68 and
-// 0.48; a pass over all vertices, with a step per neighbour to write the
-// edges, took 0.76 and 0.82.
+// the output, in the list's order.  K is what holds about 64 edges, since with
+// more the long lists of noisy regions are left to few waves, but at least four
+// runs, since a run of noise fills less than half of the lanes; and fewer where
+// that would leave less than 4,096 waves.  Above four it is odd: with a power of
+// two the blocks that share a CU come from the same part of the planes, which
+// noise fills or leaves empty together.  The list takes LDS for K runs and no
+// more, so that a CU holds all the waves it can.  A whole call, in us, at
+//                              edges/run  K = 1    4    5    8   11   23   31   32
+//   512^3 noise                       62   3548 2428 2558 2415 2488 2547 2690 2668
+//   300x280x290 Gaussian, noisy       30    565  348  338  332  337  357  370  375
+//   512^3 Gaussian sums              3.2   1151  709  652  647  566  534  538  949
+//   700x600x500 the same             1.2   1273  862  813  756  705  651  639  645
+//   512^3 Perlin noise               0.6   1199  776  732  623  544  459  445  447
+//   64^3 Gaussian sums                41     61   65   70   76   83  108  129  129
+// Up to kFewRuns runs are listed with a lane per vertex, more with a lane per
+// run (their marks are few).
+constexpr int kFewRuns = 8;
+
 __global__ void __launch_bounds__(kBlock)
 k_egraph_write(Walk w, uint64_t nruns, int K,
                const unsigned long long *__restrict__ marks,
                const int64_t *__restrict__ off,
                const int32_t *__restrict__ asc,
                const int32_t *__restrict__ desc, int32_t *__restrict__ out) {
-  __shared__ uint16_t list[kBlock / 64][64 * 64];  // run << 6 | position
+  extern __shared__ uint16_t list[];  // 64 * K per wave: run << 6 | position
   const int lane = threadIdx.x & 63;
-  uint16_t *const mine = list[threadIdx.x >> 6];
+  uint16_t *const mine = list + (threadIdx.x >> 6) * (64 * K);
   const uint64_t r0 =
       ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / 64 * (uint32_t)K;
   const uint64_t r = r0 + lane;
@@ -2297,8 +2309,20 @@ k_egraph_write(Walk w, uint64_t nruns, int K,
   }
   const uint32_t total = __shfl(inc, 63);
   uint32_t at = inc - n;
-  for (unsigned long long t = m; t; t &= t - 1)
-    mine[at++] = (uint16_t)(lane << 6 | (__ffsll((long long)t) - 1));
+  if (K > kFewRuns) {  // a lane per run
+    for (unsigned long long t = m; t; t &= t - 1)
+      mine[at++] = (uint16_t)(lane << 6 | (__ffsll((long long)t) - 1));
+  } else {  // a lane per vertex
+    for (int q = 0; q < K; ++q) {
+      const unsigned long long mq = __shfl(m, q);
+      const uint32_t base = __shfl(at, q);
+      if ((mq >> lane) & 1u)
+        mine[base + __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(mq >> 32),
+                        __builtin_amdgcn_mbcnt_lo((uint32_t)mq, 0u))] =
+            (uint16_t)(q << 6 | lane);
+    }
+  }
   __syncthreads();
   if (!total) return;  // uniform over the wave
   const uint64_t z0 = r0 / w.runs;
@@ -2464,11 +2488,13 @@ int extremum_graph_run(msc_ctx *ctx, const float *field, const int64_t *dims,
   const int64_t total = (int64_t)ctx->hctr[kCtrExtra];
   *count = total;
   if (edges && capacity >= total && total > 0) {
-    // Runs per wave: as many as hold about 32 edges.
-    const int K = (int)std::min<int64_t>(64, std::max<int64_t>(1, 32 * nc / total));
+    // Runs per wave (see k_egraph_write).
+    const int64_t least = std::max<int64_t>(1, std::min<int64_t>(4, nc / 4096)),
+                  fill = std::min<int64_t>(30, 64 * nc / total) | 1;
+    const int K = (int)std::max(least, fill);
     MSC_PHASE(ctx, s, "egraph_write", 4.0 * N + 12.0 * total,
               (marked ? k_egraph_write<<<grid64((nc + K - 1) / K * 64, kBlock),
-                                         kBlock, 0, s>>>(
+                                         kBlock, kBlock * K * 2, s>>>(
                             w, (uint64_t)nc, K, marks, off, asc, desc, edges)
                       : k_egraph_write_small<<<(unsigned)nb, kBlock, 0, s>>>(
                             field, X, Y, Z, asc, desc, off, edges)));

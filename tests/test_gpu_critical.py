@@ -141,3 +141,66 @@ def test_longest_chain(msc):
     here = torch.full((n,), 2, dtype=torch.uint8, device="cuda")
     here[0] = here[-1] = 1
     assert torch.equal(code, low | (here - low) << 4)
+
+
+@pytest.mark.parametrize("dims", [(128, 128, 130), (96, 90, 70), (300, 200, 40)])
+@pytest.mark.parametrize("kind", ["noise", "mixed", "smooth", "smoother"])
+def test_runs_per_wave(msc, dims, kind):
+    """Grids of enough runs for a wave to take 1, 2, 4, 8 and more of them, with
+    marks everywhere, in a part of the planes, and sparse: the marked walk's
+    edges equal those of the pass over blocks of 256 vertices."""
+    X, Y, Z = dims
+    f = synth.perlin_field(dims, seed=5,
+                           frequency=0.02 if kind == "smoother" else 0.1)
+    if kind in ("noise", "mixed"):
+        rough = synth.random_field(dims, seed=6)
+        f = np.where(np.arange(Z)[:, None, None] % 16 <
+                     (16 if kind == "noise" else 2), rough, f)
+    f = f.astype(np.float32)
+    t = torch.from_numpy(np.ascontiguousarray(f)).cuda()
+    a, d, _ = msc.segment(t)
+    got = msc.extremum_graph(t, a, d)
+    nb = (f.size + 255) // 256
+    small = torch.empty(4 * nb + 8 * (nb + 1) + 8192, dtype=torch.uint8,
+                        device="cuda")
+    small = small[(-small.data_ptr()) % 256:]
+    msc.set_workspace(small)
+    try:
+        want = msc.extremum_graph(t, a, d)
+    finally:
+        msc.set_workspace(None)
+    assert got.shape[0] > 0
+    assert torch.equal(got, want)
+
+
+def test_noise_costs_no_more_than_the_dense_pass(msc):
+    """A graph of pure noise takes no longer from the marked vertices than from
+    the pass that looks at every vertex (which a workspace without room for
+    the marks gets); it took 1.4 times as long when a run was listed by one
+    lane."""
+    t = torch.from_numpy(synth.random_field((256, 240, 200), seed=8)).cuda()
+    a, d, _ = msc.segment(t)
+    n = msc.extremum_graph(t, a, d).shape[0]
+    edges = torch.empty((n, 3), dtype=torch.int32, device="cuda")
+    nb = (t.numel() + 255) // 256
+    small = torch.empty(4 * nb + 8 * (nb + 1) + 8192, dtype=torch.uint8,
+                        device="cuda")
+
+    def best():
+        ms = []
+        for _ in range(8):
+            x, y = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            x.record()
+            assert msc.extremum_graph_into(t, a, d, edges) == n
+            y.record()
+            y.synchronize()
+            ms.append(x.elapsed_time(y))
+        return min(ms)
+
+    marked = best()
+    msc.set_workspace(small[(-small.data_ptr()) % 256:])
+    try:
+        dense = best()
+    finally:
+        msc.set_workspace(None)
+    assert marked < 1.2 * dense, (marked, dense)
