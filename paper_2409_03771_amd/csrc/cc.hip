@@ -284,9 +284,12 @@ __device__ __forceinline__ uint32_t mask_bits32(const uint8_t *p) {
 // pair of runs that touch, found with a few operations on the rows' words,
 // whatever the number of vertices.  What bounds the pass is the latency of its
 // steps (load, scan, unions in LDS, stores), so a tile holds four waves and a
-// CU six tiles.  At 1024^3 with 30 % in the mask it takes 0.45 ms; with a
-// thread per column, which loads its bytes one by one and unites vertex by
-// vertex, it took 2.0.
+// CU six tiles.  At 1024^3 with 30 % in the mask it takes 0.40 ms (0.43 where
+// every pair of runs is joined and none starts under another); with a thread
+// per column, which loads its bytes one by one and unites vertex by vertex, it
+// took 2.0.  Rows of many runs are the slow ones: every other vertex masked in
+// all three directions takes 0.13 ms at 256^3, columns of every other x joined by
+// full rows 0.10 (0.04 with a thread per column).
 constexpr int kCTileThreads = kCRows;
 
 template <int B>
@@ -333,39 +336,70 @@ __global__ void __launch_bounds__(kCTileThreads) k_cc_tile(CBatch<B> b) {
   base[r] = first;
   {
     uint32_t i = first;
-    for (uint32_t s = st; s; s &= s - 1, ++i) {
-      par[i] = (int32_t)i;
+    for (uint32_t s = st; s; s &= s - 1, ++i)
       head[i] = (uint16_t)(r * CTX + __ffs((int)s) - 1);
-    }
   }
   __syncthreads();
   // Edges to the rows before (y-1), (z-1) and (y-1, z-1): x touches x and x-1
   // there.  A run A = [a, b] and a run B = [c, e] of the other row touch when
   // c <= b and e >= a - 1: they overlap from max(a, c) on, where one of them
-  // starts, or B ends just before a.  An edge into the diagonal row is implied
-  // where x is masked in one of the other two rows.
-  if (m) {
-    const uint32_t ny = ly > 0 ? word[r - 1] : 0u;
-    const uint32_t nz = lz > 0 ? word[r - CTY] : 0u;
-    const uint32_t nd = ly > 0 && lz > 0 ? word[r - CTY - 1] : 0u;
-    auto join = [&](uint32_t nw, int row, uint32_t skip) {
-      const uint32_t sn = run_starts(nw);
-      const uint32_t bn = base[row];
-      for (uint32_t c = m & nw & (st | sn) & ~skip; c; c &= c - 1) {
-        const int x = __ffs((int)c) - 1;
-        uf_unite<int32_t>(par, (int32_t)(first + run_of(st, x)),
-                          (int32_t)(bn + run_of(sn, x)));
-      }
-      for (uint32_t c = st & ~nw & (nw << 1) & ~skip; c; c &= c - 1) {
-        const int x = __ffs((int)c) - 1;  // at least 1
-        uf_unite<int32_t>(par, (int32_t)(first + run_of(st, x)),
-                          (int32_t)(bn + run_of(sn, x - 1)));
-      }
-    };
-    if (ny) join(ny, r - 1, 0u);
-    if (nz) join(nz, r - CTY, 0u);
-    if (nd) join(nd, r - CTY - 1, ny | nz);
+  // starts, or B ends just before a; there is one such position for every pair
+  // of runs that touch.  An edge into the diagonal row is implied where x is
+  // masked in one of the other two rows.
+  const uint32_t ny = m && ly > 0 ? word[r - 1] : 0u;
+  const uint32_t nz = m && lz > 0 ? word[r - CTY] : 0u;
+  const uint32_t nd = m && ly > 0 && lz > 0 ? word[r - CTY - 1] : 0u;
+  auto touch = [&](uint32_t nw) {
+    return (m & nw & (st | run_starts(nw))) | (st & ~nw & (nw << 1));
+  };
+  // Number of the run of row `row` (word nw) that is touched at position x.
+  auto touched = [&](uint32_t nw, int row, int x) {
+    return base[row] + run_of(run_starts(nw), (nw >> x) & 1u ? x : x - 1);
+  };
+  // The positions of c that are the first in their run of this row.
+  auto firsts = [&](uint32_t c) {
+    uint32_t f = c, p = m;
+#pragma unroll
+    for (int k = 1; k < 32; k <<= 1) {
+      f |= p & (f << k);
+      p &= p << k;
+    }
+    return c & ~(m & (f << 1));
+  };
+  // A run starts under the first one that it touches, which has a smaller
+  // number: half of the joins at the price of a store.
+  uint32_t cy = touch(ny), cz = touch(nz), hooked = 0;
+  {
+    const uint32_t f = firsts(cy);
+    cy &= ~f;
+    for (uint32_t c = f; c; c &= c - 1) {
+      const int x = __ffs((int)c) - 1;
+      const uint32_t k = run_of(st, x);
+      hooked |= 1u << k;
+      par[first + k] = (int32_t)touched(ny, r - 1, x);
+    }
   }
+  for (uint32_t c = firsts(cz); c; c &= c - 1) {
+    const int x = __ffs((int)c) - 1;
+    const uint32_t k = run_of(st, x);
+    if ((hooked >> k) & 1u) continue;
+    hooked |= 1u << k;
+    cz &= ~(1u << x);
+    par[first + k] = (int32_t)touched(nz, r - CTY, x);
+  }
+  for (uint32_t k = 0; k < cnt; ++k)
+    if (!((hooked >> k) & 1u)) par[first + k] = (int32_t)(first + k);
+  __syncthreads();
+  auto join = [&](uint32_t c, uint32_t nw, int row) {
+    for (; c; c &= c - 1) {
+      const int x = __ffs((int)c) - 1;
+      uf_unite<int32_t>(par, (int32_t)(first + run_of(st, x)),
+                        (int32_t)touched(nw, row, x));
+    }
+  };
+  join(cy, ny, r - 1);
+  join(cz, nz, r - CTY);
+  join(touch(nd) & ~(ny | nz), nd, r - CTY - 1);
   __syncthreads();
   CTileOut *out = ctile_out(d.loc, ti);
   out->word[r] = m;

@@ -344,3 +344,21 @@ def test_csr_curves(msc, n, order):
         np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"{cut}")
         if n == 1 << 20:
             assert min(ms) < 4.0, (cut, ms)
+
+
+@pytest.mark.parametrize("dims", [(64, 48, 33), (131, 70, 1), (33, 17, 50)])
+@pytest.mark.parametrize("kind", ["comb", "teeth", "checker", "stairs", "dots"])
+def test_rows_of_many_runs(msc, dims, kind):
+    """Masks whose rows hold up to 16 runs of a tile's 32 columns, which touch
+    one long run, a run each, or only diagonally."""
+    X, Y, Z = dims
+    z, y, x = np.ogrid[:Z, :Y, :X]
+    m = {"comb": (x % 2 == 0) | (y % 16 == 5),
+         "teeth": (x % 3 != 1) & ((x % 2 == 0) | (y % 5 == 0) | (z % 4 == 2)),
+         "checker": (x + y + z) % 2 == 0,
+         "stairs": ((x + y) % 4 == 0) | ((x - z) % 5 == 0),
+         "dots": (x % 2 == 0) & (y % 2 == 0) & (z % 2 == 0)}[kind]
+    m = np.ascontiguousarray(np.broadcast_to(m, (Z, Y, X))).astype(np.uint8)
+    want, _ = O.cc_grid(m)
+    got = msc.cc_label_grid(torch.from_numpy(m).cuda())
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
