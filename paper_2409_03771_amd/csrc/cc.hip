@@ -776,8 +776,9 @@ __device__ __forceinline__ bool csr_chunk(const CsrGraph &g, int32_t v,
 
 // Hook to the smallest masked vertex among v and the first chunk of its row.
 __global__ void __launch_bounds__(kBlock)
-k_csr_init(CsrGraph g, int32_t *__restrict__ P) {
+k_csr_init(CsrGraph g, int32_t *__restrict__ P, unsigned long long *ctr) {
   const int64_t i = gid();
+  if (i < kNumCounters) ctr[i] = 0ull;  // (grids are of whole blocks)
   if (i >= g.n) return;
   const int32_t v = (int32_t)i;
   int32_t best = -1;
@@ -851,14 +852,10 @@ k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
 // see what the others have written: a leg then steps over all that the leg
 // before covered (the vertices below, whose threads started earlier, do the
 // same).
-__global__ void __launch_bounds__(kBlock)
-k_csr_compress(int64_t n, int32_t *P) {
-  const int64_t v = gid();
-  if (v >= n) return;
+__device__ __forceinline__ int32_t csr_settle(int32_t *P, int64_t v) {
   int32_t x = __hip_atomic_load(&P[v], __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-  if (x < 0) return;
-  bool open = true;
+  bool open = x >= 0;
 #pragma unroll 1
   for (int k = 0; open && k < kLeg; ++k) {
     const int32_t p = __hip_atomic_load(&P[x], __ATOMIC_RELAXED,
@@ -875,7 +872,29 @@ k_csr_compress(int64_t n, int32_t *P) {
       x = p;
     }
   }
-  __hip_atomic_store(&P[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return x;
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_csr_compress(int64_t n, int32_t *P) {
+  const int64_t v = gid();
+  if (v >= n) return;
+  const int32_t x = csr_settle(P, v);
+  if (x >= 0)
+    __hip_atomic_store(&P[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The last compression: labels below `half`, which lie below the forest, are
+// written at once.
+__global__ void __launch_bounds__(kBlock)
+k_csr_final(int64_t n, int64_t half, int32_t *P, int64_t *L) {
+  const int64_t v = gid();
+  if (v >= n) return;
+  const int32_t x = csr_settle(P, v);
+  if (v < half)
+    L[v] = (int64_t)x;
+  else if (x >= 0)
+    __hip_atomic_store(&P[v], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The root that a sample of the vertices names most often (-2: none is in the
@@ -903,9 +922,21 @@ k_csr_giant(int64_t n, const int32_t *__restrict__ P, int32_t *giant) {
       if (cur == -1 || cur == r) break;
       h = (h + 1) & (kSampleSlots - 1);
     }
-    const uint32_t c = atomicAdd(&cnt[h], 1u) + 1;
-    atomicMax(&best, (unsigned long long)c << 32 | (uint32_t)r);
+    atomicAdd(&cnt[h], 1u);
   }
+  __syncthreads();
+  unsigned long long top = 0;
+  for (int i = threadIdx.x; i < kSampleSlots; i += 1024)
+    if (cnt[i]) {
+      const unsigned long long c =
+          (unsigned long long)cnt[i] << 32 | (uint32_t)key[i];
+      top = c > top ? c : top;
+    }
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long c = __shfl_xor(top, o);
+    top = c > top ? c : top;
+  }
+  if ((threadIdx.x & 63) == 0 && top) atomicMax(&best, top);
   __syncthreads();
   if (threadIdx.x == 0) *giant = best ? (int32_t)(uint32_t)best : -2;
 }
@@ -989,7 +1020,7 @@ k_csr_widen(int64_t a, int64_t b, const int32_t *P, int64_t *L) {
 // The last stretch [a, n), at most kTail vertices, in one block: every entry
 // is read before any label is written.  `walk`: the entries are not roots yet
 // (a = 0; nothing is overwritten while the block walks).
-constexpr int kTail = 8192;
+constexpr int kTail = 16384;
 
 __global__ void __launch_bounds__(1024)
 k_csr_widen_tail(int64_t a, int64_t n, bool walk, const int32_t *P,
@@ -1165,8 +1196,10 @@ int cc_grid_batch_run(msc_ctx *ctx, int n, const msc_mask *masks,
 }
 
 // Graphs from this size on take the steps that settle most edges early (8,000
-// vertices: 89 us with them, 122 without; 1,728: 81 and 75, as each step is a
-// launch).
+// vertices of a mesh: 72 us with them, 122 without; 1,728: 81 and 75, as each
+// step is a launch.  On a curve, two entries a row, the launches are all that
+// they add up to 128k vertices: 5k 80 us and 74, 64k 115 and 96; the entry count
+// that would tell is on the device).
 constexpr int64_t kCsrLarge = 1 << 12;
 // Rounds of joins, each over one in so many waves of vertices: trees are fewer
 // and larger from round to round, so fewer attempts reach all of them.  With
@@ -1192,13 +1225,12 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   const unsigned nb = grid_for(n);
   CsrGraph g{n, row_ptr, col_idx, mask, nullptr};
   int32_t *giant = reinterpret_cast<int32_t *>(ctx->dctr + kCtrGiant);
-  MSC_TRY(clear_counters(ctx, s));
   if (large && mask) {
     g.bits = mbits;
     k_csr_mask_bits<<<nb, kBlock, 0, s>>>(n, mask, mbits);
   }
   MSC_PHASE(ctx, s, "csr_init", 17.0 * n,
-            (k_csr_init<<<nb, kBlock, 0, s>>>(g, P)));
+            (k_csr_init<<<nb, kBlock, 0, s>>>(g, P, ctx->dctr)));
   MSC_PHASE(ctx, s, "csr_compress", 8.0 * n,
             (k_csr_compress<<<nb, kBlock, 0, s>>>(n, P)));
   if (large) {
@@ -1220,7 +1252,8 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   int64_t a = 0;
   if (n > kTail) {
     MSC_PHASE(ctx, s, "csr_final", 8.0 * n,
-              (k_csr_compress<<<nb, kBlock, 0, s>>>(n, P)));
+              (k_csr_final<<<nb, kBlock, 0, s>>>(n, n / 2, P, labels)));
+    a = n / 2;
     while (n - a > kTail) {
       const int64_t b = (n + a) / 2;
       k_csr_widen<<<grid_for(b - a), kBlock, 0, s>>>(a, b, P, labels);
