@@ -1580,13 +1580,18 @@ constexpr unsigned kPairExtrema = 96;
 // A call of few tiles with more extrema than this per tile on average goes to
 // the slab pass whole, its smooth tiles too: the slowest tile of the pair pass
 // then delays nothing (200^3 Gaussian sums, mostly noise: 331 us with both
-// passes, 310 so; 223x157x101: 171 and 149; a captured batch of four 152 and
-// 136; Perlin noise, 13 a tile, would take 198 us instead of 164).  Few are
-// 2,048 tiles of one field (260^3, 2,601 tiles, loses 2 %) or 600 of several
-// (90 fields of 2,400 tiles, some of them smooth, lose 3 to 7 %).
+// passes, 310 so; 223x157x101: 171 and 149; Perlin noise, 13 a tile, would take
+// 198 us instead of 164).  Few are 2,048 tiles of one field (260^3, 2,601 tiles,
+// loses 2 %) or 1,200 of several, where some are smooth: batches of 3 to 24
+// fields take 181 us with both passes and 153 so at 492 tiles, 198 and 182 at
+// 585, 195 and 180 at 702, 235 and 222 at 937, 287 and 281 at 1,081, 297 and 288
+// or 250 and 252 at 1,250, but 325 and 337 at 1,560, 601 and 648 at 2,848.  Every
+// block adds up the fields' counts, so the fields are few too: 96 of 24^3 lose
+// 3 %, 40 of 24..90 2 %, 520 of 16^3 5 %.
 constexpr unsigned kNoisyField = 48;
 constexpr uint32_t kAloneTiles = 2048;
-constexpr uint32_t kFewTiles = 600;
+constexpr uint32_t kFewTiles = 1200;
+constexpr int kFewFields = 24;
 
 // And calls of at most this many tiles leave the pair pass out, which is a
 // launch more (64^3: 110 -> 92 us, 100x90x80 Perlin 72 -> 69; at 500 tiles
@@ -2423,12 +2428,14 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
     // table runs once more on the capacity that always suffices (the second
     // pass and its clear return at once when nothing overflowed).
     unsigned long long *const dcells = direct ? fctr + kFCells : nullptr;
+    const bool few = nfields == 1 ? nt <= kAloneTiles
+                                  : nfields <= kFewFields && nt <= kFewTiles;
     if (nt > kSlabOnlyTiles)
       MSC_PHASE(ctx, s, "tile_pairs", 13.0 * total_n,
                 (k_tile_pairs<C><<<nt, C::kThreads, 0, s>>>(
                     fds, tfield, seg, next, ctr, tstat, tlist, cidx,
                     fctr,
-                    nt <= (nfields == 1 ? kAloneTiles : kFewTiles) ? nfields : 0,
+                    few ? nfields : 0,
                     dcells)));
     const unsigned sb =
         std::min<uint64_t>((uint64_t)nt * (C::TZ / kSlabZ), kSlabBlocks);

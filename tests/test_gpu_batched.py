@@ -164,3 +164,20 @@ def test_counts_folded_at_once_and_later(msc, shapes):
         assert st["n_exits"] > 0
     st = msc.last_stats()
     assert st["jump_rounds"] >= 1 and st["exit_steps"] >= st["jump_rounds"]
+
+
+@pytest.mark.parametrize("count,dims", [(13, (96, 80, 96)), (14, (96, 80, 96)),
+                                        (24, (64, 48, 48)), (25, (64, 48, 48))])
+def test_noisy_batches(msc, count, dims):
+    """Noise with a smooth field among it, around the 1,200 tiles and the 24
+    fields up to which a call goes to the slab pass whole."""
+    fs = [synth.random_field(dims, seed=40 + i) for i in range(count - 1)]
+    fs.append(synth.gaussian_field(dims, 4, 3, noise=False))
+    outs = msc.segment_batched([torch.from_numpy(f).cuda() for f in fs])
+    for i, (f, out) in enumerate(zip(fs, outs)):
+        want = O.segment(f)
+        for g, w in zip(out, want):
+            np.testing.assert_array_equal(g.cpu().numpy(), w, err_msg=f"{i}")
+        st = msc.last_field_stats(i)
+        assert [st["n_maxima"], st["n_minima"], st["n_cells"]] == \
+            oracle_counts(want), i
