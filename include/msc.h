@@ -395,11 +395,11 @@ MSC_API int cc_label_grid_ranks(msc_ctx *ctx, const uint8_t *mask,
 /*
  * cc_label_grid for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
- * labels, with no context and no allocation of any kind.  The tile-local
- * roots live in a static device array of 2^27 16-bit entries (256 MiB on
- * each GPU the library runs on, held until the process ends), taken on the
- * call's first use on a device.  The roots are stored by whole 32x16x16
- * tiles, so a call may cover at most 2^14 tiles: ceil(X/32) * ceil(Y/16) *
+ * labels, with no context and no allocation of any kind.  Each 32x16x16
+ * tile's rows (as bits) and tile-local roots live in a slot of 16 KB of a
+ * static device array of 256 MiB (on each GPU the library runs on, held until
+ * the process ends), taken on the call's first use on a device, so a call may
+ * cover at most 2^14 tiles: ceil(X/32) * ceil(Y/16) *
  * ceil(Z/16) <= 16384 (512^3 vertices, or fewer when the sides are not
  * multiples of the tile).
  *

@@ -21,7 +21,9 @@
 //              touching tile-local roots only (the paper's ghost exchange);
 //   cc_final   label = root of the vertex's run's tile-local root.
 // CSR graphs have no locality to exploit: hooks to a smaller masked neighbour,
-// unions along the listed edges, then a final find per vertex.
+// single attempts to join trees across sampled edges, a bitmap of the largest
+// tree, unions along the listed edges that it does not settle, then a final
+// walk per vertex.
 #include <algorithm>
 #include <climits>
 #include <mutex>
@@ -641,7 +643,9 @@ __global__ void __launch_bounds__(kCRows) k_cc_root_shift(CBatch<B> b) {
 //    edge leave nearly everything of a large component in one; the tree that a
 //    sample of the vertices names most often is marked in a bitmap, and the
 //    pass over all edges gathers one bit for each edge of a marked vertex and
-//    goes on only where a bit is clear.
+//    goes on only where a bit is clear.  (Sampling edges first and skipping the
+//    most frequent component is the Afforest scheme of Sutton, Ben-Nun and
+//    Barak, IPDPS 2018; the one-shot joins and the bitmap are this file's.)
 // Every edge of every row is still examined, so rows that list an edge in one
 // direction only are as good as symmetric ones.  50M vertices with 30 % in the
 // mask take 6.3 ms instead of 14.2 (the union pass 2.6 instead of 8.9, the
@@ -1315,15 +1319,15 @@ int jump_run(msc_ctx *ctx, int64_t *d, int64_t n, int rounds, int sync,
 
 // ---------------------------------------------------------------------------
 // Grid CC with no allocation (for callers that cannot allocate: code under
-// graph capture, tight serving loops).  The tile-local roots live in one
-// static device array per GPU, taken once per device by symbol address.
+// graph capture, tight serving loops).  The tiles' slots live in one static
+// device array per GPU, taken once per device by symbol address.
 // ---------------------------------------------------------------------------
 
 namespace {
 
-// 16-bit tile-local root per vertex, stored by whole tiles: 2^27 entries
-// (256 MiB per GPU the library runs on, held until the process ends) bound a
-// call at 2^14 tiles of 32x16x16 (512^3 vertices).
+// A slot of 2^13 16-bit words per tile (see CTileOut): 2^27 words (256 MiB per
+// GPU the library runs on, held until the process ends) bound a call at 2^14
+// tiles of 32x16x16 (512^3 vertices).
 constexpr int64_t kNoAllocEntries = INT64_C(1) << 27;
 static __device__ __align__(256) uint16_t scratch[kNoAllocEntries];
 

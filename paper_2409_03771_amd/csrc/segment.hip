@@ -1404,9 +1404,10 @@ __global__ void k_table_clear(unsigned long long *keys, int32_t *vals,
 }
 
 // Linear probing gives up after kTableProbes slots: an insert that finds no
-// room reports an overflow (the host then grows the table and runs the pair
-// pass again), and a lookup stops there too, since every key sits within
-// that many slots of its hash.
+// room reports an overflow, and a lookup stops there too, since every key sits
+// within that many slots of its hash.  After an overflow the cells are worked
+// out again on a larger table, which a grid's call takes on the device and a
+// mesh's on the host.
 constexpr uint32_t kTableProbes = 512;
 
 // Insert (key, id) keeping the smallest id; reads before each atomic so that
