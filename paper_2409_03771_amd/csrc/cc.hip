@@ -628,8 +628,8 @@ __global__ void __launch_bounds__(kCRows) k_cc_root_shift(CBatch<B> b) {
 // CSR graphs
 // ---------------------------------------------------------------------------
 //
-// What bounds this path is random gathers, one per listed edge and pass: about
-// 52 G/s from an array that the last-level cache holds (256 MB), fewer from a
+// What bounds this path is random gathers, one per listed edge and pass: 50 to
+// 60 G/s from an array that the last-level cache holds (256 MB), fewer from a
 // larger one, and several times more from one that fits the L2s (4 MB each).
 // So:
 //  - the forest is 32-bit (n <= INT32_MAX) and lives in the upper half of the
@@ -648,7 +648,7 @@ __global__ void __launch_bounds__(kCRows) k_cc_root_shift(CBatch<B> b) {
 //    Barak, IPDPS 2018; the one-shot joins and the bitmap are this file's.)
 // Every edge of every row is still examined, so rows that list an edge in one
 // direction only are as good as symmetric ones.  50M vertices with 30 % in the
-// mask take 6.3 ms instead of 14.2 (the union pass 2.6 instead of 8.9, the
+// mask take 5.7 ms instead of 14.2 (the union pass 2.7 instead of 8.9, the
 // hooks 1.1 instead of 3.9, the joins 0.8), 1M vertices without a mask 0.25
 // instead of 0.73.
 

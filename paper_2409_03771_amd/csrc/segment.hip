@@ -100,12 +100,16 @@ struct FieldDev {
 
 // Calls of at most this many tiles fold their counters with one atomic per
 // tile where the count is made, and resolve their exits without an order: most
-// of those blocks are resident at once, and the same-address atomics (10 ns
-// each) end within the kernels.  Larger calls fold per-tile records in kernels
-// of their own and sort the tiles.  Each launch costs 3 to 5 us: with the line
-// at 512 instead of 4,096, 200^3 takes 184 us instead of 164 and 90 fields of
-// 30..100 take 480 us instead of 438; at 20,000, Perlin noise at 512^3 (16,384
-// tiles) takes 1.67 ms instead of 1.63.
+// of those blocks are resident at once, and the same-address atomics (three a
+// tile, 10 ns each) end within the kernels.  Larger calls fold per-tile records
+// in kernels of their own and sort the tiles.  Each launch costs 3 to 5 us: with
+// the line at 512 instead of 4,096, 200^3 takes 184 us instead of 164 and 90
+// fields of 30..100 take 480 us instead of 438; at 20,000, Perlin noise at 512^3
+// (16,384 tiles) takes 1.67 ms instead of 1.63.  Tiles of 2,048 vertices are done
+// in less than half the time of their atomics, so their line is a quarter of
+// that: 200x190x180 Perlin noise in 3,864 tiles of 32x8x8 takes 257 us with them
+// (105 in the tile pass) and 208 without (51); tiles of 4,096 vertices are as
+// good either way (2,208 of them 196 and 207, 2,016 206 and 214).
 constexpr uint32_t kDirectTiles = 4096;
 
 // A tile's exits in the list: `base`, then `na` ascent exits and `nd`
@@ -2363,7 +2367,8 @@ int segment_batch(msc_ctx *ctx, int nfields, const msc_field *fields,
                           : nullptr;
 
   CallRec &R = ctx->calls[rec];
-  const bool direct = nt <= kDirectTiles;
+  const bool direct =
+      nt <= (C::kThreads * C::TZ < 4096 ? kDirectTiles / 4 : kDirectTiles);
   {
     auto setup = [&](auto b) {
       constexpr int B = decltype(b)::value;

@@ -181,3 +181,48 @@ def test_noisy_batches(msc, count, dims):
         st = msc.last_field_stats(i)
         assert [st["n_maxima"], st["n_minima"], st["n_cells"]] == \
             oracle_counts(want), i
+
+
+@pytest.mark.parametrize("tile,dims", [((32, 8, 8), (1024, 256, 1)),
+                                       ((32, 8, 8), (1024, 257, 1)),
+                                       ((32, 8, 16), (1024, 1024, 1)),
+                                       ((32, 8, 16), (1025, 1024, 1)),
+                                       ((64, 8, 16), (130, 100, 90))])
+def test_counts_of_smaller_tiles(msc, tile, dims):
+    """Labels and counts on both sides of where a call of smaller tiles folds
+    its counters in passes of their own."""
+    f = synth.random_field(dims, seed=sum(dims), levels=7)
+    want = O.segment(f)
+    msc.set_tile(*tile)
+    try:
+        out = msc.segment(torch.from_numpy(f).cuda())
+        st = msc.last_stats()
+    finally:
+        msc.set_tile(*msc.tile_shapes()[0])
+    for g, w in zip(out, want):
+        np.testing.assert_array_equal(g.cpu().numpy(), w)
+    assert [st["n_maxima"], st["n_minima"], st["n_cells"]] == \
+        oracle_counts(want)
+    assert st["jump_rounds"] >= 1 and st["exit_steps"] >= st["jump_rounds"]
+
+
+def test_small_tiles_do_not_queue_on_their_counters(msc):
+    """3,864 tiles of 32x8x8: the tile pass takes about as long as with tiles
+    of 32x16x16, not twice as long (one atomic per tile and counter)."""
+    f = synth.perlin_field((200, 190, 180), 3, device="cuda", z_chunk=180)
+    ms = {}
+    try:
+        for tile in ((32, 16, 16), (32, 8, 8)):
+            msc.set_tile(*tile)
+            best = None
+            for _ in range(8):
+                msc.profile(True)
+                msc.segment(f)
+                torch.cuda.synchronize()
+                t = msc.profile_read()["tile_local"]["total_ms"]
+                best = t if best is None else min(best, t)
+            ms[tile] = best
+    finally:
+        msc.profile(False)
+        msc.set_tile(*msc.tile_shapes()[0])
+    assert ms[(32, 8, 8)] < 1.5 * ms[(32, 16, 16)], ms
