@@ -215,8 +215,10 @@ int msc_create(msc_ctx **out, int device) {
     return MSC_ENOMEM;
   }
   std::memset(c->hctr, 0, msc::kNumCounters * sizeof(unsigned long long));
-  bool ev_ok = hipEventCreateWithFlags(&c->done, hipEventDisableTiming) ==
-               hipSuccess;
+  bool ev_ok = hipHostGetDevicePointer(reinterpret_cast<void **>(&c->dhctr),
+                                       c->hctr, 0) == hipSuccess &&
+               hipEventCreateWithFlags(&c->done, hipEventDisableTiming) ==
+                   hipSuccess;
   for (int k = 0; ev_ok && k < msc::kPinnedSlots; ++k)
     ev_ok = hipEventCreateWithFlags(&c->slots[k].copied,
                                     hipEventDisableTiming) == hipSuccess;

@@ -657,10 +657,14 @@ constexpr int kEdgeChunk = 8;
 
 // Unions of v with u[j] for every j with need[j]: the roots of v and of
 // those u[j] are found first with all the walks side by side (each step's
-// loads for every walk issued before any is used; walks that are done, or
-// not needed, reload a root harmlessly), then each u[j]'s root is hooked to
-// v's in turn, the smaller root winning.  A hook whose root has moved
-// meanwhile walks that pair again and retries; the merged root is then v's.
+// loads for every walk issued before any is used; walks that are done, or not
+// needed, reload v's own entry harmlessly, not a root's, where everyone's loads
+// queue up: 1M vertices of a curve in no order 327 -> 290 us), then each u[j]'s
+// root is hooked to v's in turn, the smaller root winning.  A hook whose root has
+// moved meanwhile walks that pair again and retries; the merged root is then v's.
+// (Hooking under any smaller member of the other tree, which spares reading its
+// root, makes everyone's compare-and-swaps meet on the large tree's root instead:
+// 100,000 vertices with 100,000 random edges 175 -> 234 us.)
 __device__ __forceinline__ void uf_unite_row_dev(
     int32_t *par, int32_t v, const int32_t (&u)[kEdgeChunk],
     const bool (&need)[kEdgeChunk]) {
@@ -681,9 +685,9 @@ __device__ __forceinline__ void uf_unite_row_dev(
     if (!any) break;
     int32_t pr[W], gr[W];
 #pragma unroll
-    for (int i = 0; i < W; ++i) pr[i] = ld_dev(&par[r[i]]);
+    for (int i = 0; i < W; ++i) pr[i] = ld_dev(&par[open[i] ? r[i] : v]);
 #pragma unroll
-    for (int i = 0; i < W; ++i) gr[i] = ld_dev(&par[pr[i]]);
+    for (int i = 0; i < W; ++i) gr[i] = ld_dev(&par[open[i] ? pr[i] : v]);
 #pragma unroll
     for (int i = 0; i < W; ++i) {
       if (!open[i]) continue;
@@ -825,10 +829,8 @@ __device__ __forceinline__ int32_t uf_root_near(const int32_t *P, int32_t x) {
 // until the trees are one has a million threads queue up on a handful of roots
 // (1.5 ms), and walking on along a curve with rising ids, where the hooks form
 // one chain, takes up to 20 ms for 1M vertices.
-__global__ void __launch_bounds__(kBlock)
-k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
-  const int64_t w = gid() >> 6;
-  const int64_t i = w * stride * 64 + (threadIdx.x & 63);
+__device__ __forceinline__ void csr_join(const CsrGraph &g, int32_t *P,
+                                         int64_t i, int pick) {
   if (i >= g.n) return;
   int32_t a = P[i];
   if (a < 0) return;
@@ -847,6 +849,23 @@ k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
     __hip_atomic_compare_exchange_strong(&P[hi], &hi, lo, __ATOMIC_RELAXED,
                                          __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_csr_join(CsrGraph g, int32_t *P, int stride, int pick) {
+  csr_join(g, P, (gid() >> 6) * stride * 64 + (threadIdx.x & 63), pick);
+}
+
+// The rounds after the first in one launch, for graphs where a launch costs more
+// than the order of the rounds is worth.
+template <int S1, int S2, int S3>
+__global__ void __launch_bounds__(kBlock)
+k_csr_join_rest(CsrGraph g, int32_t *P) {
+  const int64_t w = gid() >> 6;
+  const int64_t i = w * S1 * 64 + (threadIdx.x & 63);
+  csr_join(g, P, i, 1);
+  if (w % (S2 / S1) == 0) csr_join(g, P, i, 2);
+  if (w % (S3 / S1) == 0) csr_join(g, P, i, 3);
 }
 
 // Every vertex straight to its root.  Most trees are shallow, but hooks and
@@ -902,35 +921,35 @@ k_csr_final(int64_t n, int64_t half, int32_t *P, int64_t *L) {
 }
 
 // The root that a sample of the vertices names most often (-2: none is in the
-// mask), into *giant.  One block; a guess, which only speed depends on.
-constexpr int kSample = 2048, kSampleSlots = 4096;
-
-__global__ void __launch_bounds__(1024)
-k_csr_giant(int64_t n, const int32_t *__restrict__ P, int32_t *giant) {
-  __shared__ int32_t key[kSampleSlots];
-  __shared__ uint32_t cnt[kSampleSlots];
+// mask), found by a block of T threads; a guess, which only speed depends on.
+template <int T, int SAMPLE>
+__device__ __forceinline__ int32_t csr_giant(int64_t n,
+                                             const int32_t *__restrict__ P) {
+  constexpr int SLOTS = 2 * SAMPLE, LOG = __builtin_ctz(SLOTS);
+  __shared__ int32_t key[SLOTS];
+  __shared__ uint32_t cnt[SLOTS];
   __shared__ unsigned long long best;
-  for (int i = threadIdx.x; i < kSampleSlots; i += 1024) {
+  for (int i = threadIdx.x; i < SLOTS; i += T) {
     key[i] = -1;
     cnt[i] = 0;
   }
   if (threadIdx.x == 0) best = 0;
   __syncthreads();
-  for (int k = threadIdx.x; k < kSample; k += 1024) {
+  for (int k = threadIdx.x; k < SAMPLE; k += T) {
     const int32_t r =
         P[(uint64_t)((uint32_t)k * 0x9e3779b1u) * (uint64_t)n >> 32];
     if (r < 0) continue;
-    uint32_t h = ((uint32_t)r * 0x85ebca6bu) >> 20;
+    uint32_t h = ((uint32_t)r * 0x85ebca6bu) >> (32 - LOG);
     for (;;) {  // half the slots stay empty
       const int32_t cur = atomicCAS(&key[h], -1, r);
       if (cur == -1 || cur == r) break;
-      h = (h + 1) & (kSampleSlots - 1);
+      h = (h + 1) & (SLOTS - 1);
     }
     atomicAdd(&cnt[h], 1u);
   }
   __syncthreads();
   unsigned long long top = 0;
-  for (int i = threadIdx.x; i < kSampleSlots; i += 1024)
+  for (int i = threadIdx.x; i < SLOTS; i += T)
     if (cnt[i]) {
       const unsigned long long c =
           (unsigned long long)cnt[i] << 32 | (uint32_t)key[i];
@@ -942,7 +961,23 @@ k_csr_giant(int64_t n, const int32_t *__restrict__ P, int32_t *giant) {
   }
   if ((threadIdx.x & 63) == 0 && top) atomicMax(&best, top);
   __syncthreads();
-  if (threadIdx.x == 0) *giant = best ? (int32_t)(uint32_t)best : -2;
+  return best ? (int32_t)(uint32_t)best : -2;
+}
+
+__global__ void __launch_bounds__(1024)
+k_csr_giant(int64_t n, const int32_t *__restrict__ P, int32_t *giant) {
+  const int32_t r = csr_giant<1024, 2048>(n, P);
+  if (threadIdx.x == 0) *giant = r;
+}
+
+// The tree's vertices as a bitmap: from the root that k_csr_giant has found, or
+// (in graphs where a launch costs more) that every block finds for itself.
+__global__ void __launch_bounds__(kBlock)
+k_csr_mark_small(int64_t n, const int32_t *__restrict__ P, uint32_t *bits) {
+  const int32_t r = csr_giant<kBlock, 512>(n, P);
+  const int64_t v = gid();
+  const bool on = v < n && P[v] == r;
+  if (((v | 63) - 63) < n) put_bits(bits, v, on);
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -1023,13 +1058,18 @@ k_csr_widen(int64_t a, int64_t b, const int32_t *P, int64_t *L) {
 
 // The last stretch [a, n), at most kTail vertices, in one block: every entry
 // is read before any label is written.  `walk`: the entries are not roots yet
-// (a = 0; nothing is overwritten while the block walks).
+// (a = 0; nothing is overwritten while the block walks).  The call's last kernel:
+// it also hands the counters to the host, where a copy would take longer.
 constexpr int kTail = 16384;
 
 __global__ void __launch_bounds__(1024)
 k_csr_widen_tail(int64_t a, int64_t n, bool walk, const int32_t *P,
-                 int64_t *L) {
+                 int64_t *L, const unsigned long long *ctr,
+                 unsigned long long *hctr) {
   constexpr int K = kTail / 1024;
+  if (threadIdx.x < kNumCounters)
+    __hip_atomic_store(hctr + threadIdx.x, ctr[threadIdx.x], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
   int32_t r[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -1215,6 +1255,12 @@ constexpr int64_t kCsrLarge = 1 << 12;
 constexpr int kJoinStride[] = {1, 4, 16, 32};
 constexpr int64_t kJoinHalf = 1 << 21;
 constexpr int kJoins = sizeof(kJoinStride) / sizeof(int);
+// Up to so many vertices the rounds after the first share a launch (mesh of 20^3:
+// 71 -> 60 us, 10,000 vertices and random edges 97 -> 91), and the tree to mark
+// is found by every block for itself (curve of 64k vertices 115 -> 106).  Rounds
+// in one launch see less of each other's joins: 100,000 vertices with 200,000
+// random entries take 276 us so, 144 in launches of their own.
+constexpr int64_t kJoinFused = 1 << 14, kMarkFused = 1 << 17;
 
 int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
                const int32_t *col_idx, const uint8_t *mask, int64_t *labels,
@@ -1238,7 +1284,8 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
   MSC_PHASE(ctx, s, "csr_compress", 8.0 * n,
             (k_csr_compress<<<nb, kBlock, 0, s>>>(n, P)));
   if (large) {
-    for (int k = 0; k < kJoins; ++k) {
+    const bool fused = n <= kJoinFused;
+    for (int k = 0; k < (fused ? 1 : kJoins); ++k) {
       const int stride = kJoinStride[k] * (n >= kJoinHalf ? 2 : 1);
       const int64_t waves = (n + 64 * stride - 1) / (64 * stride);
       MSC_PHASE(ctx, s, "csr_join", 21.0 * n,
@@ -1246,10 +1293,21 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
                                                                     stride, k)));
       if (k == 0) k_csr_compress<<<nb, kBlock, 0, s>>>(n, P);
     }
+    static_assert(kJoins == 4, "the rounds of k_csr_join_rest");
+    if (fused)
+      MSC_PHASE(ctx, s, "csr_join", 21.0 * n,
+                (k_csr_join_rest<kJoinStride[1], kJoinStride[2], kJoinStride[3]>
+                 <<<grid_for((n + 64 * kJoinStride[1] - 1) /
+                             (64 * kJoinStride[1]) * 64),
+                    kBlock, 0, s>>>(g, P)));
     k_csr_compress<<<nb, kBlock, 0, s>>>(n, P);
-    MSC_PHASE(ctx, s, "csr_mark", 4.0 * n,
-              (k_csr_giant<<<1, 1024, 0, s>>>(n, P, giant),
-               k_csr_giant_bits<<<nb, kBlock, 0, s>>>(n, P, giant, marked)));
+    if (n <= kMarkFused)
+      MSC_PHASE(ctx, s, "csr_mark", 4.0 * n,
+                (k_csr_mark_small<<<nb, kBlock, 0, s>>>(n, P, marked)));
+    else
+      MSC_PHASE(ctx, s, "csr_mark", 4.0 * n,
+                (k_csr_giant<<<1, 1024, 0, s>>>(n, P, giant),
+                 k_csr_giant_bits<<<nb, kBlock, 0, s>>>(n, P, giant, marked)));
   }
   MSC_PHASE(ctx, s, "csr_union", 13.0 * n,
             (k_csr_union<<<nb, kBlock, 0, s>>>(g, P, marked, ctx->dctr)));
@@ -1264,9 +1322,11 @@ int cc_csr_run(msc_ctx *ctx, int64_t n, const int64_t *row_ptr,
       a = b;
     }
   }
-  k_csr_widen_tail<<<1, 1024, 0, s>>>(a, n, a == 0, P, labels);
+  k_csr_widen_tail<<<1, 1024, 0, s>>>(a, n, a == 0, P, labels, ctx->dctr,
+                                      ctx->dhctr);
   MSC_HIP_TRY(hipGetLastError());
-  MSC_TRY(read_counters(ctx, s));
+  MSC_HIP_TRY(hipStreamSynchronize(s));
+  if (ctx->prof.on) ctx->prof.flush();
   if (ctx->hctr[kCtrBadIndex]) return MSC_EINVAL;
   ctx->stats = msc_stats{};
   ctx->stats.n_vertices = n;

@@ -167,6 +167,7 @@ struct msc_ctx {
   // Device counters and a pinned host mirror.
   unsigned long long *dctr = nullptr;
   unsigned long long *hctr = nullptr;
+  unsigned long long *dhctr = nullptr;  // the mirror as the device addresses it
   msc_stats stats{};
   msc::Profiler prof;
   int tile_choice = 0;         // segmentation tile shape (0 = default)

@@ -362,3 +362,20 @@ def test_rows_of_many_runs(msc, dims, kind):
     want, _ = O.cc_grid(m)
     got = msc.cc_label_grid(torch.from_numpy(m).cuda())
     np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n", [1 << 14, (1 << 14) + 1, 1 << 17, (1 << 17) + 1])
+@pytest.mark.parametrize("deg", [1, 4])
+def test_csr_sizes_of_shared_launches(msc, n, deg):
+    """On both sides of where the rounds of joins share a launch and where
+    every block finds the tree to mark, sparse (many small trees) and dense."""
+    rng = np.random.default_rng(n + deg)
+    rp = np.arange(n + 1, dtype=np.int64) * deg
+    col = rng.integers(0, n, size=n * deg).astype(np.int32)
+    for mask in (None, (rng.random(n) < 0.6).astype(np.uint8)):
+        want, _ = O.cc_csr(rp, col, mask)
+        np.testing.assert_array_equal(gpu_cc_csr(msc, rp, col, mask), want)
+    bad = col.copy()
+    bad[-1] = n
+    with pytest.raises(msc.MscError):
+        gpu_cc_csr(msc, rp, bad)
