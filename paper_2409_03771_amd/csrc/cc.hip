@@ -1240,10 +1240,11 @@ int cc_grid_batch_run(msc_ctx *ctx, int n, const msc_mask *masks,
 }
 
 // Graphs from this size on take the steps that settle most edges early (8,000
-// vertices of a mesh: 72 us with them, 122 without; 1,728: 81 and 75, as each
-// step is a launch.  On a curve, two entries a row, the launches are all that
-// they add up to 128k vertices: 5k 80 us and 74, 64k 115 and 96; the entry count
-// that would tell is on the device).
+// vertices of a mesh, ids in no order: 64 us with them, 122 without; 1,728: 81
+// and 75, as each step is a launch.  Where rows are short or ids lie in order the
+// launches are all that they add up to 128k vertices: 16k of a curve 104 us and
+// 80, 8,000 of a mesh in grid order 63 and 53; the entry count that would tell
+// is on the device).
 constexpr int64_t kCsrLarge = 1 << 12;
 // Rounds of joins, each over one in so many waves of vertices: trees are fewer
 // and larger from round to round, so fewer attempts reach all of them.  With
